@@ -43,6 +43,7 @@
 #include "../../include/mone_swiglu.h"
 #include "host_common.hpp"
 #include "swiglu_kernels.hpp"
+#include "swiglu_step.hpp"
 
 using namespace mone;
 
@@ -59,6 +60,7 @@ struct SwLayout {
   int G, sets;
   long long kh_ss, kt_ss, dy_ss, dyt_ss, rate_ss, vpart_ss, beta_ss;
   size_t kpre, kh, kt, dy, dyt, dat, at, dzgt, wig, woc, rope, gate, loss_part, loss_out;
+  size_t rq, ra, rwo;  // the read's queries K_q, hidden activations A and W_out^T copy
   size_t rate, vpart, beta, n_ig, n_out;  // paper optimiser
   size_t total;
 };
@@ -125,21 +127,33 @@ SwLayout make_sw_layout(const mone_swiglu_config* c) {
   const size_t NS = G > 1 ? 2 : 1;
   L.G = (int)G;
   L.sets = (int)NS;
-  L.kh_ss = L.dy_ss = (long long)(B * Tp * dhp);
-  L.kt_ss = L.dyt_ss = (long long)(B * dh * Tp);
+  // bf16: K and dY0 as token and channel fragments (32 * ceil(d_h / 32) channels per token)
+  const bool bf = c->act_dtype == MONE_BF16;
+  const size_t dhf = (size_t)round_up(c->d_head, 32);
+  L.kh_ss = L.dy_ss = (long long)(B * Tp * (bf ? dhf : dhp));
+  L.kt_ss = L.dyt_ss = (long long)(B * (bf ? dhf : dh) * Tp);
   L.rate_ss = (long long)(nl * Tp);
   L.vpart_ss = (long long)(nl * (Tp / kRateTokens));
   L.beta_ss = (long long)nl;
   L.kpre = take(nl * G * Tp * d * E);
-  L.kh = take(NS * G * B * Tp * dhp * E);
-  L.kt = take(NS * G * B * dh * Tp * E);
-  L.dy = take(NS * G * B * Tp * dhp * E);
-  L.dyt = take(NS * G * B * dh * Tp * E);
-  L.dat = take(B * dh * Tp * E);
-  L.at = take(B * dh * Tp * E);
-  L.dzgt = take(B * 2 * dh * Tp * E);
+  L.kh = take(NS * G * (size_t)L.kh_ss * E);
+  L.kt = take(NS * G * (size_t)L.kt_ss * E);
+  L.dy = take(NS * G * (size_t)L.dy_ss * E);
+  L.dyt = take(NS * G * (size_t)L.dyt_ss * E);
   L.wig = take(B * 2 * dh * dhp * E);
-  L.woc = take(B * dh * dhp * E);
+  if (bf) {  // the step keeps its intermediates on chip; the read has buffers of its own
+    L.rq = take(B * Tp * dhp * E);
+    L.ra = take(B * Tp * dhp * E);
+    L.rwo = take(B * dh * dhp * E);
+  } else {
+    L.dat = take(B * dh * Tp * E);
+    L.at = take(B * dh * Tp * E);
+    L.dzgt = take(B * 2 * dh * Tp * E);
+    L.woc = take(B * dh * dhp * E);
+    L.rq = L.kh;
+    L.ra = L.dy;
+    L.rwo = L.dat;
+  }
   L.rope = take(Tp * (dh / 2) * 8);
   L.gate = take(nl * Tp * (size_t)c->n_heads * 4);
   L.loss_part = take(B * (size_t)L.parts_max * 4);
@@ -202,6 +216,7 @@ int run_sw_prep(mone_swiglu* H, const void* x, long long lsx, int n, int g, int 
   // rows of a segment in the batched launches; one segment keeps its padded extent
   const int seg_rows = g > 1 ? n : Tp, kpre_rows = Ly.G * Tp;
   const int nz = g > 1 ? g * n : (int)round_up(n, 64);  // token rows KEYS writes
+  constexpr bool kFrag = sizeof(E) == 2;
   float* rate = PAPER ? H->at<float>(Ly.rate) + c0 * Ly.rate_ss : nullptr;
   hipError_t e;
 
@@ -249,7 +264,7 @@ int run_sw_prep(mone_swiglu* H, const void* x, long long lsx, int n, int g, int 
   // KEYS: per-token L2 norm per head and RoPE -> K, K^T
   {
     H->timer.begin(MONE_SW_STAGE_KEYS, s);
-    sw_keys_kernel<E><<<dim3(nz / 64, NH, L), dim3(256), 0, s>>>(
+    sw_keys_kernel<E, kFrag><<<dim3(nz / 64, NH, L), dim3(256), 0, s>>>(
         H->at<E>(Ly.kpre), d, NH, dh, dhp, Tp, H->at<float2>(Ly.rope),
         H->at<E>(Ly.kh) + c0 * Ly.kh_ss, H->at<E>(Ly.kt) + c0 * Ly.kt_ss, seg_rows, kpre_rows,
         Ly.kh_ss, Ly.kt_ss);
@@ -259,10 +274,48 @@ int run_sw_prep(mone_swiglu* H, const void* x, long long lsx, int n, int g, int 
   return MONE_OK;
 }
 
-// The weight-dependent part of the step of one segment of n tokens whose preprocessing is in
-// copy `cp`: DA, FWD and UPD.
-template <typename E, bool PAPER>
-int run_sw_update(mone_swiglu* H, int n, int cp, hipStream_t s) {
+// The weight-dependent part of the steps of g consecutive segments of n tokens whose
+// preprocessing is in copies cp ..: one launch for bf16 activations.
+template <bool PAPER>
+int run_sw_step(mone_swiglu* H, int n, int cp, int g, hipStream_t s) {
+  const mone_swiglu_config& c = H->cfg;
+  const SwLayout& Ly = H->lay;
+  SwStep p{};
+  p.kf = H->at<bf16_t>(Ly.kh) + cp * Ly.kh_ss;
+  p.kt = H->at<bf16_t>(Ly.kt) + cp * Ly.kt_ss;
+  p.yf = H->at<bf16_t>(Ly.dy) + cp * Ly.dy_ss;
+  p.yt = H->at<bf16_t>(Ly.dyt) + cp * Ly.dyt_ss;
+  p.k_ss = Ly.kh_ss;
+  p.y_ss = Ly.dy_ss;
+  if (PAPER) {
+    p.rate = H->at<float>(Ly.rate) + cp * Ly.rate_ss;
+    p.beta = H->at<float>(Ly.beta) + cp * Ly.beta_ss;
+    p.rate_ss = Ly.rate_ss;
+    p.beta_ss = Ly.beta_ss;
+    p.m_in = H->opt.mom_in; p.m_gate = H->opt.mom_gate; p.m_out = H->opt.mom_out;
+    p.n_ig = H->at<float>(Ly.n_ig);
+    p.n_out = H->at<float>(Ly.n_out);
+  }
+  p.w_in = H->w.w_in; p.w_gate = H->w.w_gate; p.w_out = H->w.w_out;
+  p.wig = H->at<bf16_t>(Ly.wig);
+  p.loss_part = H->at<float>(Ly.loss_part);
+  p.dh = c.d_head; p.dhp = Ly.dhp; p.H = c.n_heads; p.Tp = Ly.Tp; p.n = n; p.g = g;
+  p.B = c.n_layers * c.n_heads;
+  p.parts = 4 * ((c.d_head + 31) / 32);
+  p.lr = c.lr;
+  H->timer.begin(MONE_SW_STAGE_UPD, s);
+  const hipError_t e = launch_sw_step(p, PAPER, s);
+  if (e != hipSuccess) return hip_fail(e, "launch STEP");
+  H->timer.end(MONE_SW_STAGE_UPD, s);
+  H->last_parts = p.parts;
+  H->last_n = n;
+  return MONE_OK;
+}
+
+// fp32 activations: the step as three launches (DA, FWD, UPD) through memory.
+template <bool PAPER>
+int run_sw_step_f32(mone_swiglu* H, int n, int cp, hipStream_t s) {
+  using E = float;
   const mone_swiglu_config& c = H->cfg;
   const SwLayout& Ly = H->lay;
   const int L = c.n_layers, NH = c.n_heads, dh = c.d_head, B = L * NH;
@@ -365,12 +418,22 @@ int run_sw_update(mone_swiglu* H, int n, int cp, hipStream_t s) {
   return MONE_OK;
 }
 
+template <typename E, bool PAPER>
+int run_sw_update(mone_swiglu* H, int n, int cp, int g, hipStream_t s) {
+  if constexpr (sizeof(E) == 2) return run_sw_step<PAPER>(H, n, cp, g, s);
+  for (int i = 0; i < g; ++i) {
+    const int rc = run_sw_step_f32<PAPER>(H, n, cp + i, s);
+    if (rc != MONE_OK) return rc;
+  }
+  return MONE_OK;
+}
+
 // One segment of n tokens: its preprocessing into copy 0, then its update.  x [L][n][d], layer
 // stride lsx.
 template <typename E, bool PAPER>
 int run_sw_segment(mone_swiglu* H, const void* x, long long lsx, int n, hipStream_t s) {
   const int rc = run_sw_prep<E, PAPER>(H, x, lsx, n, 1, 0, s);
-  return rc != MONE_OK ? rc : run_sw_update<E, PAPER>(H, n, 0, s);
+  return rc != MONE_OK ? rc : run_sw_update<E, PAPER>(H, n, 0, 1, s);
 }
 
 // S whole segments from x [L][S*T][d] (layer stride lsx): preprocessing in batches of up to G
@@ -388,12 +451,7 @@ int run_sw_segments(mone_swiglu* H, const void* x, long long lsx, int S, hipStre
   const int nb = (S + G - 1) / G;
   auto xs = [&](int b) { return reinterpret_cast<const E*>(x) + (long long)b * G * T * d; };
   auto gsz = [&](int b) { return S - b * G < G ? S - b * G : G; };
-  auto steps = [&](int b, int c0) {
-    int rc = MONE_OK;
-    for (int cp = 0; cp < gsz(b) && rc == MONE_OK; ++cp)
-      rc = run_sw_update<E, PAPER>(H, T, c0 + cp, s);
-    return rc;
-  };
+  auto steps = [&](int b, int c0) { return run_sw_update<E, PAPER>(H, T, c0, gsz(b), s); };
   if (nb < 2 || H->lay.sets < 2) {
     for (int b = 0; b < nb; ++b) {
       int rc = run_sw_prep<E, PAPER>(H, xs(b), lsx, T, gsz(b), 0, s);
@@ -446,9 +504,9 @@ int run_sw_read(mone_swiglu* H, const mone_swiglu_reader* rd, const void* xq, in
   const int Tp = Ly.Tp, dhp = Ly.dhp, D = 2 * rd->d_kv;
   const int qz = (int)round_up(q, 64);
   E* qpre = H->at<E>(Ly.kpre);  // the queries before normalisation, then the memory tokens h
-  E* kq = H->at<E>(Ly.kh);
-  E* abuf = H->at<E>(Ly.dy);    // A [B][Tp][d_hp]; its padding columns are always zero
-  E* wot = H->at<E>(Ly.dat);    // W_out^T [B][d_h][d_hp]
+  E* kq = H->at<E>(Ly.rq);
+  E* abuf = H->at<E>(Ly.ra);    // A [B][Tp][d_hp]; its padding columns are always zero
+  E* wot = H->at<E>(Ly.rwo);    // W_out^T [B][d_h][d_hp]
   float* gate = H->at<float>(Ly.gate);
   const TileShape tq = q <= 64 ? TILE_64x256 : TILE_128x128;
   hipError_t e;
@@ -476,8 +534,8 @@ int run_sw_read(mone_swiglu* H, const mone_swiglu_reader* rd, const void* xq, in
   }
   // QKEYS: per-head L2 norm and RoPE at positions 0 .. q-1
   H->timer.begin(MONE_SW_STAGE_QKEYS, s);
-  sw_keys_kernel<E><<<dim3(qz / 64, NH, L), dim3(256), 0, s>>>(
-      qpre, d, NH, dh, dhp, Tp, H->at<float2>(Ly.rope), kq, H->at<E>(Ly.kt), Tp, Tp, 0LL, 0LL);
+  sw_keys_kernel<E, false><<<dim3(qz / 64, NH, L), dim3(256), 0, s>>>(
+      qpre, d, NH, dh, dhp, Tp, H->at<float2>(Ly.rope), kq, nullptr, Tp, Tp, 0LL, 0LL);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "launch QKEYS");
   H->timer.end(MONE_SW_STAGE_QKEYS, s);
   // QFWD: A = SiLU(Z) * G with [Z | G] = K_q W_ig^T; and the W_out^T copy for QOUT
@@ -562,9 +620,10 @@ hipError_t build_copies(mone_swiglu* H, hipStream_t s) {
   const mone_swiglu_config& c = H->cfg;
   const SwLayout& Ly = H->lay;
   const int dh = c.d_head, B = c.n_layers * c.n_heads;
-  const long long per = 3LL * dh * Ly.dhp;
+  const long long per = (sizeof(E) == 2 ? 2LL : 3LL) * dh * Ly.dhp;
   sw_pack_kernel<E><<<dim3((unsigned)((per + 255) / 256), B), dim3(256), 0, s>>>(
-      H->w.w_in, H->w.w_gate, H->w.w_out, dh, Ly.dhp, H->at<E>(Ly.wig), H->at<E>(Ly.woc));
+      H->w.w_in, H->w.w_gate, H->w.w_out, dh, Ly.dhp, H->at<E>(Ly.wig),
+      sizeof(E) == 2 ? nullptr : H->at<E>(Ly.woc));
   return hipGetLastError();
 }
 

@@ -13,12 +13,26 @@
 namespace mone {
 namespace {
 
+// Element offsets of the memory step's operand fragments (bf16; layouts in swiglu_step.hpp) for
+// head b: 8 channels ch .. ch+7 of token t, and 8 tokens t .. t+7 of channel ch.
+__device__ __forceinline__ long long tok_frag(int b, int t, int ch, int Tp, int dh) {
+  const int nb = (dh + 31) >> 5;
+  return (long long)b * Tp * 32 * nb +
+         ((long long)(t >> 5) * 2 * nb + (ch >> 4)) * 512 + (((ch >> 3) & 1) * 32 + (t & 31)) * 8;
+}
+__device__ __forceinline__ long long chan_frag(int b, int t, int ch, int Tp, int dh) {
+  const int nb = (dh + 31) >> 5;
+  return (long long)b * Tp * 32 * nb +
+         ((long long)(t >> 4) * nb + (ch >> 5)) * 512 + (((t >> 3) & 1) * 32 + (ch & 31)) * 8;
+}
+
 // PROJ: tile of X [P_k ; P_v]^T = [raw keys | raw values] [tokens][2d], with the elementwise
 // part of the preprocessing fused:
 //   key columns    SiLU(s r + b) per channel  -> K' [L][Tp][d] (normalised and rotated by the
 //                  KEYS kernel)
 //   value columns  v = SiLU(r)                -> dY0 = -v / n [B][Tp][d_hp] (row pass) and
-//                  dY^T = -eta v / n [B][d_h][Tp] (column pass, from v left in the staging)
+//                  dY^T = -eta v / n [B][d_h][Tp] (column pass, from v left in the staging);
+//                  bf16: dY0 in the memory step's token and channel fragments instead
 // Tokens >= n are stored as 0.  d and d_h are multiples of 8, so a chunk never straddles the
 // key/value boundary or a head.
 // Several consecutive segments in one launch: GEMM row r is token t = r % seg_rows of segment
@@ -36,6 +50,7 @@ struct EpiSwProj : EpiBase {
   int d, dh, dhp, H, Tp, n;
   int seg_rows, kpre_rows;
   long long dy_ss, dyt_ss, rate_ss;
+  static constexpr bool kFrag = sizeof(E) == 2;
   __device__ __forceinline__ bool has_cols(int) const { return true; }
   __device__ __forceinline__ float rows8(int, int l, int row, int col, int, int, float (&v)[8],
                                          const float (&)[8]) const {
@@ -58,7 +73,10 @@ struct EpiSwProj : EpiBase {
         v[i] = sv;
         o[i] = -sv * inv_n;
       }
-      store8(dy + sg * dy_ss + (((long long)l * H + e) * Tp + t) * dhp + ch, o);
+      if constexpr (kFrag)
+        store8(dy + sg * dy_ss + tok_frag(l * H + e, t, ch, Tp, dh), o);
+      else
+        store8(dy + sg * dy_ss + (((long long)l * H + e) * Tp + t) * dhp + ch, o);
     }
     return 0.0f;
   }
@@ -67,6 +85,13 @@ struct EpiSwProj : EpiBase {
     if (col < d) return;
     const int sg = row / seg_rows, t = row - sg * seg_rows;
     const int c = col - d, e = c / dh, ch = c - e * dh;
+    if constexpr (kFrag) {
+      float o[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) o[i] = -v[i] * inv_n;
+      store8(dyt + sg * dyt_ss + chan_frag(l * H + e, t, ch, Tp, dh), o);
+      return;
+    }
     const float* rt = rate ? rate + sg * rate_ss + (long long)l * Tp + t : nullptr;
     float o[8];
 #pragma unroll
@@ -399,8 +424,10 @@ __global__ void sw_rope_table_kernel(float2* __restrict__ tab, int Tp, int dh, d
 // padding columns) and, through LDS, K^T [B][d_h][Tp].  Each half-wave (32 lanes) takes one
 // token, lane i of it the 8 channels [8i, 8i + 8) as one 16-byte vector; the partner channels
 // of vector i (RoPE pairs c and c + d_h/2) are vector i +- d_h/16, fetched by shuffle (d_h is a
-// multiple of 16 and at most 256).  Tokens >= n hold zeros in K' and stay zero.
-template <typename E>
+// multiple of 16 and at most 256).  Tokens >= n hold zeros in K' and stay zero.  FRAG: K and K^T
+// go to the memory step's token and channel fragments instead, both through LDS (whole 1 KiB
+// fragments).  kt null (not FRAG): K only.
+template <typename E, bool FRAG>
 __global__ __launch_bounds__(256) void sw_keys_kernel(const E* __restrict__ kpre, int d, int H,
                                                       int dh, int dhp, int Tp,
                                                       const float2* __restrict__ rope,
@@ -463,8 +490,33 @@ __global__ __launch_bounds__(256) void sw_keys_kernel(const E* __restrict__ kpre
 #pragma unroll
       for (int i = 0; i < 8; ++i) tile[t][c + i] = from_f32<E>(o[i]);
     }
-    if (c < dhp) store8(kh + ((long long)b * Tp + j) * dhp + c, o);
+    if constexpr (!FRAG) {
+      if (c < dhp) store8(kh + ((long long)b * Tp + j) * dhp + c, o);
+    }
   }
+  if constexpr (FRAG) {
+    __syncthreads();
+    // 64 tokens: 2 blocks of 32 x 2 nb channel steps, 4 blocks of 16 x nb channel blocks
+    const int nb = (dh + 31) >> 5, nf = 4 * nb * 64;
+    for (int i = threadIdx.x; i < nf; i += 256) {
+      const int ln = i & 63, f = i >> 6, tb = f / (2 * nb), s = f - tb * 2 * nb;
+      const int t = 32 * tb + (ln & 31), ch = 16 * s + 8 * (ln >> 5);
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = ch < dh ? to_f32(tile[t][ch + k]) : 0.0f;
+      store8(kh + tok_frag(b, j0 + t, ch, Tp, dh), v);
+    }
+    for (int i = threadIdx.x; i < nf; i += 256) {
+      const int ln = i & 63, f = i >> 6, ts = f / nb, cb = f - ts * nb;
+      const int t = 16 * ts + 8 * (ln >> 5), ch = 32 * cb + (ln & 31);
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = ch < dh ? to_f32(tile[t + k][ch]) : 0.0f;
+      store8(kt + chan_frag(b, j0 + t, ch, Tp, dh), v);
+    }
+    return;
+  }
+  if (!kt) return;
   __syncthreads();
   // K^T: 8 threads per channel row, 8 tokens (one vector) each
   for (int i = threadIdx.x; i < dh * 8; i += 256) {
@@ -477,7 +529,7 @@ __global__ __launch_bounds__(256) void sw_keys_kernel(const E* __restrict__ kpre
 }
 
 // The MFMA copies of the fast weights: W_ig [B][2 d_h][d_hp] (row 2i = W_in row i, row 2i + 1
-// = W_gate row i) and W_out [B][d_h][d_hp], zero in the padding columns.
+// = W_gate row i) and, unless woc is null, W_out [B][d_h][d_hp], zero in the padding columns.
 // Grid (ceil(3 d_h d_hp / 256), B).
 template <typename E>
 __global__ __launch_bounds__(256) void sw_pack_kernel(const float* __restrict__ w_in,
@@ -487,7 +539,7 @@ __global__ __launch_bounds__(256) void sw_pack_kernel(const float* __restrict__ 
                                                       E* __restrict__ woc) {
   const int b = blockIdx.y;
   const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= 3LL * dh * dhp) return;
+  if (i >= (woc ? 3LL : 2LL) * dh * dhp) return;
   const int r = (int)(i / dhp), c = (int)(i - (long long)r * dhp);
   const long long wb = (long long)b * dh * dh;
   float v = 0.0f;

@@ -1,0 +1,386 @@
+// The fused memory step of the paper-form memory (see swiglu_step.hpp for the operand layouts).
+//
+// Everything a segment's step computes for hidden unit i of a head needs only row i of W_in,
+// W_gate and W_out (z_i, g_i and dA_i are dot products with those rows, and the three gradients
+// are the rows dZ_i K, dG_i K and A_i dY), and so does the row renormalisation.  So a workgroup
+// owns 32 hidden units of one head, keeps their rows (fp32 masters and momenta) in its registers
+// and runs segment after segment with no exchange between workgroups: the weights are read and
+// written once per launch and no intermediate reaches memory.
+//
+// Per chunk of 128 tokens (4 waves, 256 threads):
+//   phase 1  wave w takes tokens 32 w .. of the chunk: Z, G and dA0 [32 tokens][32 units] over the
+//            channels (A operand: token fragments from memory, B operand: the bf16 rows in LDS);
+//            then dZ = eta dA0 g SiLU'(z), dG = eta dA0 SiLU(z) and eta A as bf16 into LDS
+//   phase 2  wave w takes channel blocks w and w + 4: the gradients [32 channels][32 units] over
+//            the chunk's tokens (A operand: channel fragments from memory, B: the LDS exchange).
+//            Their accumulators have the layout of the masters and momenta, so the update is
+//            elementwise in registers; a row's channels lie in lanes l and l + 32 of the 4 waves.
+// No operand fragment is used by two waves of a workgroup, so the fragments go from L2 straight
+// into registers, phase 1's of the next chunk during phase 2 and phase 2's during phase 1.
+#include "swiglu_step.hpp"
+
+#include "kernels.hpp"
+
+namespace mone {
+namespace {
+
+constexpr int kRows = 32;    // hidden units per workgroup
+constexpr int kChunk = 128;  // tokens per chunk
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x16 mfma(const u32x4& a, const u32x4& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// This wave's LDS accesses are done; global loads stay in flight over the barrier.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_s_waitcnt((63 & 15) | ((63 >> 4) << 14) | (7 << 4));  // lgkmcnt(0)
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+template <int NB, bool PAPER>
+struct StepLds {
+  static constexpr int NK = 2 * NB;           // contraction steps over the channels (16 each)
+  static constexpr int CPW = (NB + 3) / 4;    // channel blocks per wave, at most
+  // momenta of the first ML matrices live in LDS, the others (and all masters) in registers: what
+  // the register file has no room for beside the prefetched fragments
+  static constexpr int ML = !PAPER || CPW == 1 ? 0 : NB <= 7 ? 2 : 1;
+  static constexpr int EXC = 3 * kRows * kChunk * 2;  // exchange [3][32 units][128 tokens] bf16
+  alignas(1024) unsigned char wts[3 * NK * 1024];  // bf16 rows, B fragments [3][NK][64][16 bytes]
+  alignas(1024) unsigned char exch[2 * EXC];
+  f32x4 mom[ML > 0 ? ML * CPW * 4 * 256 : 1];
+  float ssq[3 * 4 * kRows];
+  float eta[4][32];  // rates of each wave's tokens
+};
+
+// The work of one wave, which owns channel blocks wave + 4 j for j < CPW.
+template <int NB, int CPW, bool PAPER>
+__device__ __forceinline__ void step_wave(const SwStep& P, StepLds<NB, PAPER>& S, int wave) {
+  using Lds = StepLds<NB, PAPER>;
+  constexpr int NK = Lds::NK, ML = Lds::ML, EXC = Lds::EXC, MC = Lds::CPW;
+  constexpr int CA = CPW > 0 ? CPW : 1;  // array extents
+  constexpr int KS = kChunk / 16;      // contraction steps over a chunk's tokens
+  constexpr int PD = 4;                // phase 2 fragments are loaded PD steps ahead
+  unsigned char* const wts = S.wts;
+  f32x4* const mlds = S.mom;
+  float* const ssq = S.ssq;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, hf = lane >> 5;
+  // workgroups of one XCD (bid % 8) take a contiguous run of (head, row block): a head's blocks
+  // read the same fragments through one L2
+  const int nrb = (P.dh + kRows - 1) / kRows, total = (int)gridDim.x, full = total - total % 8;
+  int v = blockIdx.x;
+  if (v < full) v = (v % 8) * (full / 8) + v / 8;
+  const int b = v / nrb, rb = v - b * nrb, l = b / P.H;
+  const int dh = P.dh, row = rb * kRows + li;  // this lane's hidden unit
+  const bool row_ok = row < dh;
+
+  float* const wp[3] = {P.w_in, P.w_gate, P.w_out};
+  float* const mp[3] = {P.m_in, P.m_gate, P.m_out};
+  const long long wbase = (long long)b * dh * dh + (long long)row * dh;
+  // element e of quad q of channel block j: channel 32 (wave + 4 j) + 8 q + 4 hf + e
+  auto chan = [&](int j, int q) { return (wave + 4 * j) * 32 + 8 * q + 4 * hf; };
+  f32x4 w[3][CA][4], m[3 - ML][CA][4];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int j = 0; j < CPW; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = chan(j, q);
+        const bool ok = row_ok && c < dh;  // d_h is a multiple of 16
+        f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+        w[a][j][q] = ok ? *reinterpret_cast<const f32x4*>(wp[a] + wbase + c) : z;
+        if constexpr (PAPER) {
+          const f32x4 x = ok ? *reinterpret_cast<const f32x4*>(mp[a] + wbase + c) : z;
+          if (a < ML) mlds[((a * MC + j) * 4 + q) * 256 + tid] = x;
+          else m[a - ML][j][q] = x;
+        }
+      }
+  float n0[3] = {0.0f, 0.0f, 0.0f};
+  if constexpr (PAPER) {
+    if (row_ok) {
+      n0[0] = P.n_ig[(long long)b * 2 * dh + 2 * row];
+      n0[1] = P.n_ig[(long long)b * 2 * dh + 2 * row + 1];
+      n0[2] = P.n_out[(long long)b * dh + row];
+    }
+  }
+  // the rows' bf16 copies as B fragments: lane l of fragment (a, s) holds unit l % 32, channels
+  // 16 s + 8 (l / 32) ..
+  auto put_weights = [&] {
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int j = 0; j < CPW; ++j) {
+        const int cb = wave + 4 * j;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 x = w[a][j][q];
+          uint2 p;
+          p.x = pack_bf16(x[0], x[1]);
+          p.y = pack_bf16(x[2], x[3]);
+          *reinterpret_cast<uint2*>(wts + ((a * NK + 2 * cb + (q >> 1)) * 64 + (q & 1) * 32 +
+                                           li) * 16 + hf * 8) = p;
+        }
+      }
+  };
+  put_weights();
+
+  f32x16 acc[3][CA];
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int j = 0; j < CPW; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[a][j][r] = 0.0f;
+
+  const int nb32 = (P.n + 31) / 32, nch = (nb32 + 3) / 4;
+  const long long hs = (long long)P.Tp * 32 * NB;  // elements of one head's fragments
+  const uint32_t voff = lane * 16;
+  const long long hb = (long long)b * hs * 2;      // this head's byte offset in every stream
+  auto frag = [&](const char* p, int i) { return *reinterpret_cast<const u32x4*>(p + voff + i * 1024); };
+  // Fragments past the segment's tokens (up to the end of its last chunk, inside the buffers) are
+  // finite leftovers of earlier segments; their products vanish with the exchange's zeros.
+  u32x4 kf[NK], yf[NK];
+  // phase 1 fragments [s0, s1) of this wave's tokens in chunk c of segment sg
+  auto load1 = [&](int sg, int c, int s0, int s1) {
+    const long long so = (long long)(4 * c + wave) * NK * 1024 + hb;
+    const char* pk = reinterpret_cast<const char*>(P.kf + sg * P.k_ss) + so;
+    const char* py = reinterpret_cast<const char*>(P.yf + sg * P.y_ss) + so;
+#pragma unroll
+    for (int s = 0; s < NK; ++s) {
+      if (s < s0 || s >= s1) continue;
+      kf[s] = frag(pk, s);
+      yf[s] = frag(py, s);
+    }
+  };
+  u32x4 kt[PD][CA], yt[PD][CA];
+  auto load2 = [&](int sg, int c, int s) {
+    const long long so = ((long long)(KS * c + s) * NB + wave) * 1024 + hb;
+    const char* pk = reinterpret_cast<const char*>(P.kt + sg * P.k_ss) + so;
+    const char* py = reinterpret_cast<const char*>(P.yt + sg * P.y_ss) + so;
+#pragma unroll
+    for (int j = 0; j < CPW; ++j) {
+      kt[s % PD][j] = frag(pk, 4 * j);
+      yt[s % PD][j] = frag(py, 4 * j);
+    }
+  };
+
+  // the rates of this wave's tokens in chunk c of segment sg (lane li: token li)
+  float etar = P.lr;
+  auto load_rate = [&](int sg, int c) {
+    if constexpr (PAPER)
+      etar = P.rate[sg * P.rate_ss + (long long)l * P.Tp + (4 * c + wave) * 32 + li];
+  };
+
+  load_rate(0, 0);
+  load1(0, 0, 0, NK);
+  int buf = 0;
+  for (int sg = 0; sg < P.g; ++sg) {
+    lds_barrier();  // the rows in LDS are those this segment starts from
+    float loss = 0.0f;
+    for (int c = 0; c < nch; ++c) {
+      // ---- phase 1
+      if (hf == 0) S.eta[wave][li] = etar;
+      f32x16 sz, sgt, sd;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sz[r] = sgt[r] = sd[r] = 0.0f;
+      auto wfrag = [&](int a, int s) {
+        return *reinterpret_cast<const u32x4*>(wts + ((a * NK + s) * 64 + lane) * 16);
+      };
+      // LDS fragments are read one step ahead; the scheduling barriers keep the compiler from
+      // hoisting later steps' reads (which would spill)
+      u32x4 bw[2][3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) bw[0][a] = wfrag(a, 0);
+#pragma unroll
+      for (int s = 0; s < NK; ++s) {
+        if (s + 1 < NK) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) bw[(s + 1) & 1][a] = wfrag(a, s + 1);
+        }
+        sz = mfma(kf[s], bw[s & 1][0], sz);
+        sgt = mfma(kf[s], bw[s & 1][1], sgt);
+        sd = mfma(yf[s], bw[s & 1][2], sd);
+#pragma unroll
+        for (int p = (s * PD) / NK; p < ((s + 1) * PD) / NK; ++p) load2(sg, c, p);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // register r = 4 q + e: token 32 (4 c + wave) + 8 q + 4 hf + e, unit li
+      unsigned char* ex = S.exch + buf * EXC;
+      const int t0 = (4 * c + wave) * 32 + 4 * hf;
+      if ((4 * c + wave) * 32 + 32 > P.n) {  // tokens past the end contribute zeros
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (t0 + 8 * (r >> 2) + (r & 3) >= P.n) sz[r] = sgt[r] = sd[r] = 0.0f;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 eta = *reinterpret_cast<const f32x4*>(&S.eta[wave][8 * q + 4 * hf]);
+        float dz[4], dg[4], av[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float z = sz[4 * q + e], g = sgt[4 * q + e], da = sd[4 * q + e];
+          const float s = sigmoidf_(z);
+          const float si = z * s, a = si * g;
+          const float eda = eta[e] * da;
+          dz[e] = eda * g * (s * (1.0f + z * (1.0f - s)));
+          dg[e] = eda * si;
+          av[e] = eta[e] * a;
+          loss += a * da;
+        }
+        const int at = (li * 16 + ((wave * 4 + q) ^ (li & 15))) * 16 + hf * 8;
+        uint2 p;
+        p.x = pack_bf16(dz[0], dz[1]); p.y = pack_bf16(dz[2], dz[3]);
+        *reinterpret_cast<uint2*>(ex + at) = p;
+        p.x = pack_bf16(dg[0], dg[1]); p.y = pack_bf16(dg[2], dg[3]);
+        *reinterpret_cast<uint2*>(ex + kRows * kChunk * 2 + at) = p;
+        p.x = pack_bf16(av[0], av[1]); p.y = pack_bf16(av[2], av[3]);
+        *reinterpret_cast<uint2*>(ex + 2 * kRows * kChunk * 2 + at) = p;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      lds_barrier();
+      // ---- phase 2; the exchange alternates between two buffers, so one barrier per chunk
+      const bool last = c + 1 == nch;
+      // (after the last chunk: the first one again, never used)
+      const int sg_n = last ? (sg + 1 < P.g ? sg + 1 : 0) : sg, c_n = last ? 0 : c + 1;
+      auto xfrag = [&](int a, int s) {
+        return *reinterpret_cast<const u32x4*>(ex + a * kRows * kChunk * 2 +
+                                               (li * 16 + ((2 * s + hf) ^ (li & 15))) * 16);
+      };
+      load_rate(sg_n, c_n);
+      u32x4 bx[2][3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) bx[0][a] = xfrag(a, 0);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        if (s + 1 < KS) {
+#pragma unroll
+          for (int a = 0; a < 3; ++a) bx[(s + 1) & 1][a] = xfrag(a, s + 1);
+        }
+#pragma unroll
+        for (int j = 0; j < CPW; ++j) {
+          acc[0][j] = mfma(kt[s % PD][j], bx[s & 1][0], acc[0][j]);
+          acc[1][j] = mfma(kt[s % PD][j], bx[s & 1][1], acc[1][j]);
+          acc[2][j] = mfma(yt[s % PD][j], bx[s & 1][2], acc[2][j]);
+        }
+        if (s + PD < KS) load2(sg, c, s + PD);
+        load1(sg_n, c_n, (s * NK) / KS, ((s + 1) * NK) / KS);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      buf ^= 1;
+    }
+    // ---- update: register 4 q + e of acc[a][j] is element e of w[a][j][q]
+    float ss[3] = {0.0f, 0.0f, 0.0f};
+    const float bt = PAPER ? P.beta[sg * P.beta_ss + l] : 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int j = 0; j < CPW; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          f32x4 gr;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            gr[e] = acc[a][j][4 * q + e];
+            acc[a][j][4 * q + e] = 0.0f;
+          }
+          if constexpr (PAPER) {
+            f32x4& lm = mlds[a < ML ? ((a * MC + j) * 4 + q) * 256 + tid : 0];
+            const f32x4 mu = a < ML ? lm : m[a < ML ? 0 : a - ML][j][q];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) gr[e] = bt * mu[e] + gr[e];
+            if (a < ML) lm = gr;
+            else m[a - ML][j][q] = gr;
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float x = w[a][j][q][e] - gr[e];
+            w[a][j][q][e] = x;
+            if constexpr (PAPER) ss[a] += x * x;
+          }
+        }
+    if constexpr (PAPER) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        ss[a] += __shfl_xor(ss[a], 32, 64);
+        if (hf == 0) ssq[(a * 4 + wave) * kRows + li] = ss[a];
+      }
+      lds_barrier();
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const float* p = ssq + a * 4 * kRows + li;
+        const float tot = ((p[0] + p[kRows]) + p[2 * kRows]) + p[3 * kRows];
+        const float sc = tot > 0.0f ? n0[a] * rsqrtf(tot) : 1.0f;
+#pragma unroll
+        for (int j = 0; j < CPW; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[a][j][q][e] *= sc;
+      }
+    }
+    put_weights();
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off, 64);
+    if (lane == 0) P.loss_part[(long long)b * P.parts + rb * 4 + wave] = loss;
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int j = 0; j < CPW; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = chan(j, q);
+        if (!row_ok || c >= dh) continue;
+        const f32x4 x = w[a][j][q];
+        *reinterpret_cast<f32x4*>(wp[a] + wbase + c) = x;
+        if constexpr (PAPER)
+          *reinterpret_cast<f32x4*>(mp[a] + wbase + c) =
+              a < ML ? mlds[((a * MC + j) * 4 + q) * 256 + tid] : m[a < ML ? 0 : a - ML][j][q];
+        if (a < 2) {
+          uint2 p;
+          p.x = pack_bf16(x[0], x[1]);
+          p.y = pack_bf16(x[2], x[3]);
+          *reinterpret_cast<uint2*>(P.wig + ((long long)b * 2 * dh + 2 * row + a) * P.dhp + c) = p;
+        }
+      }
+}
+
+template <int NB, bool PAPER>
+__global__ __launch_bounds__(256, 1) void sw_step_kernel(SwStep P) {
+  __shared__ StepLds<NB, PAPER> S;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // NB blocks over 4 waves: the first waves own one more (both paths pass the same barriers)
+  constexpr int most = (NB + 3) / 4;
+  if (wave < NB - 4 * (most - 1)) step_wave<NB, most, PAPER>(P, S, wave);
+  else step_wave<NB, most - 1, PAPER>(P, S, wave);
+}
+
+template <bool PAPER>
+hipError_t launch_nb(const SwStep& p, hipStream_t s) {
+  const dim3 grid((unsigned)(p.B * ((p.dh + kRows - 1) / kRows))), block(256);
+  switch ((p.dh + 31) / 32) {
+    case 1: sw_step_kernel<1, PAPER><<<grid, block, 0, s>>>(p); break;
+    case 2: sw_step_kernel<2, PAPER><<<grid, block, 0, s>>>(p); break;
+    case 3: sw_step_kernel<3, PAPER><<<grid, block, 0, s>>>(p); break;
+    case 4: sw_step_kernel<4, PAPER><<<grid, block, 0, s>>>(p); break;
+    case 5: sw_step_kernel<5, PAPER><<<grid, block, 0, s>>>(p); break;
+    case 6: sw_step_kernel<6, PAPER><<<grid, block, 0, s>>>(p); break;
+    case 7: sw_step_kernel<7, PAPER><<<grid, block, 0, s>>>(p); break;
+    case 8: sw_step_kernel<8, PAPER><<<grid, block, 0, s>>>(p); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_sw_step(const SwStep& p, bool paper, hipStream_t s) {
+  return paper ? launch_nb<true>(p, s) : launch_nb<false>(p, s);
+}
+
+}  // namespace mone
