@@ -218,6 +218,10 @@ def sw_stage_work(cfg, prep=1):
     # momentum's read and write with the paper's optimiser, whose row renormalisation happens
     # in the same epilogue)
     upd_w = 3 * dh * dh * (8 + E + (8 if paper else 0))
+    # bf16: one launch does the memory steps of `prep` segments (keys and dY0 in two layouts in;
+    # the masters and momenta in and out once, and the reads' copy of W_in and W_gate out)
+    step = (g * B * 2 * T * 6 * dh * dh,
+            B * (4 * g * dh * T * E + 3 * dh * dh * (16 if paper else 8) + 2 * dh * dh * E))
     return {
         "rate": (g * L * 4 * T * d, g * L * (T * d * E + 2 * d * 4 + T * 4)),
         # the projections with the elementwise preprocessing fused: X and P in; K', dY0 and
@@ -227,7 +231,7 @@ def sw_stage_work(cfg, prep=1):
         "keys": (0, 3 * g * L * T * d * E),
         "da": (B * 2 * T * dh * dh, B * (dh * dh + 2 * T * dh) * E),
         "fwd": (B * 2 * T * 2 * dh * dh, B * (2 * dh * dh + 5 * T * dh) * E + L * T * 4),
-        "upd": (B * 2 * T * 3 * dh * dh, B * (5 * dh * T * E + upd_w)),
+        "upd": step if E == 2 else (B * 2 * T * 3 * dh * dh, B * (5 * dh * T * E + upd_w)),
     }
 
 
@@ -439,6 +443,8 @@ def run_swiglu(args):
     dfl, dby = work[dom]
     davg = dms / dcnt / 1e3
     kname = {"keys": "sw_keys_kernel", "rate": "rate_kernel"}.get(dom, f"gemm_nt_kernel ({dom})")
+    if dom == "upd" and cfg.act_dtype == "bf16":
+        kname = "sw_step_kernel"
     roof = roofline(kname, dfl, dby, davg, peak)
     counted = (counted_traffic(dom, "hbm_traffic_sw_qwen0.5b.json")
                if cfg.name == "sw_qwen0.5b" and cfg.optimizer == "paper" else None)

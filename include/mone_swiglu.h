@@ -122,7 +122,8 @@ int mone_swiglu_segment(mone_swiglu* h, const void* x, int32_t n_tokens, void* s
  * The preprocessing that does not depend on the fast weights (the paper optimiser's rates and
  * decay, the key/value projections with their affine step and SiLU, the keys' normalisation
  * and segment-local RoPE) runs once for up to prep_segments segments at a time, as larger
- * launches; each segment's memory step (DA, FWD, UPD) then follows in order.  With more than
+ * launches; the segments' memory steps then follow in order (bf16 activations: one launch per
+ * batch, which keeps the fast weights on chip from segment to segment).  With more than
  * one such batch, the preprocessing of the next batch runs on an internal stream of the handle
  * (default priority) beside the memory steps of the current one; the internal stream starts
  * after the work queued on `stream` before the call and `stream` waits for it before the call's
@@ -180,11 +181,14 @@ int mone_swiglu_destroy(mone_swiglu* h);
 #define MONE_SW_STAGE_PROJ 1   /* [P_k x ; P_v x] for every token (one grouped GEMM) with the
                                   keys' affine step and SiLU and the values' SiLU fused */
 #define MONE_SW_STAGE_KEYS 2   /* keys: per-token L2 norm per head and RoPE; K and K^T */
-#define MONE_SW_STAGE_DA 3     /* dA^T = W_out dY^T per head: the hidden activations' gradient */
+#define MONE_SW_STAGE_DA 3     /* dA^T = W_out dY^T per head: the hidden activations' gradient
+                                  (fp32 activations; with bf16 part of the one UPD launch) */
 #define MONE_SW_STAGE_FWD 4    /* [Z | G]^T = [W_in ; W_gate] K^T per head; epilogue: A^T,
-                                  dZ^T, dG^T and the loss partials */
+                                  dZ^T, dG^T and the loss partials (as DA) */
 #define MONE_SW_STAGE_UPD 5    /* the three weight gradients and the update (one launch; with
-                                  MONE_OPT_PAPER also the momentum and the row renormalisation) */
+                                  MONE_OPT_PAPER also the momentum and the row renormalisation);
+                                  bf16 activations: the whole memory step, one launch for the
+                                  segments of a preprocessing batch */
 #define MONE_SW_STAGE_QPROJ 6  /* read: P_q x_q with the affine step and SiLU; the gates */
 #define MONE_SW_STAGE_QKEYS 7  /* read: L2 norm and RoPE of the queries */
 #define MONE_SW_STAGE_QFWD 8   /* read: A = SiLU(Z) * G per head */

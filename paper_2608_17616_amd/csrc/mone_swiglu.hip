@@ -6,6 +6,8 @@
 // up to 256; d_hp = d_h rounded up to 64, padding columns zero):
 //   caller state   W_in, W_gate, W_out [L][H][d_h][d_h] fp32; P [L][2d][d] act; s, b [L][d]
 //   workspace      K'   [L][Tp][d] act     keys after the affine step and SiLU
+//                  bf16: K and dY0 as the fragments of swiglu_step.hpp, in both orders, in place
+//                  of the next four; of the rest only W_ig, and K_q, A and W_out^T for the read
 //                  K    [B][Tp][d_hp]      preprocessed keys (B operand of FWD)
 //                  K^T  [B][d_h][Tp]       (B operand of the W_in / W_gate gradients)
 //                  dY0  [B][Tp][d_hp]      -v / n (B operand of DA)
@@ -17,7 +19,7 @@
 //                  W_ig [B][2 d_h][d_hp], W_out copy [B][d_h][d_hp]  MFMA copies
 //                  RoPE table [Tp][d_h/2] (cos, sin); read gates [L][Tp][H]; loss partials;
 //                  loss [L]
-// The read reuses the step's scratch: K' holds the pre-normalisation queries and then the memory
+// The read reuses the step's scratch (fp32): K' holds the pre-normalisation queries and then the memory
 // tokens h, K the queries, dY0 the hidden activations A (row-major, zero padding) and dA0^T's
 // space the transposed W_out copy.
 //                  paper optimiser (fp32): rates [L][Tp], decay block sums
@@ -30,6 +32,9 @@
 //   PROJ    [raw K | raw V] = X [P_k ; P_v]^T   epilogue: keys: affine, SiLU -> K';
 //                                               values: SiLU -> dY0, dY^T
 //   KEYS    K': per-token L2 norm per head, RoPE -> K, K^T
+//   STEP    bf16: everything below in one kernel (swiglu_step.hip), for all the segments of a
+//           preprocessing batch
+//   fp32:
 //   DA      dA0^T = W_out dY0^T
 //   FWD     [Z | G]^T = W_ig K^T     epilogue: A^T, [dZ | dG]^T, loss partials
 //   UPD     A^T dY and [dZ | dG]^T K  (2 problems)  epilogue: update of the masters + copies

@@ -16,7 +16,17 @@
 //            Their accumulators have the layout of the masters and momenta, so the update is
 //            elementwise in registers; a row's channels lie in lanes l and l + 32 of the 4 waves.
 // No operand fragment is used by two waves of a workgroup, so the fragments go from L2 straight
-// into registers, phase 1's of the next chunk during phase 2 and phase 2's during phase 1.
+// into registers, phase 1's of the next chunk during the elementwise part and phase 2's during
+// phase 1.
+//
+// 32 units per workgroup: their state fills the register file of one CU (one workgroup per CU;
+// the momenta of two matrices sit in LDS), and at 4 heads of 224 over 24 layers the 672
+// workgroups make 2.6 rounds.  Measured there (512-token segments, 8 per launch, the paper's
+// optimiser): 600 us a launch against 8 x 177 us for the three launches per segment it replaces
+// (DA, FWD and UPD through memory, 20 + 53 + 105 us).  What bounds it: about 8.3K cycles a chunk,
+// of which the MFMAs are 2.9K; the fragments' 224 KB a chunk take 3.6K cycles of the CU's 64
+// bytes a cycle from L2, the elementwise part 2.3K, partly one after the other with one wave per
+// SIMD; and the state's 230 MB read and written once per launch, about 0.12 ms.
 #include "swiglu_step.hpp"
 
 #include "kernels.hpp"
@@ -26,12 +36,19 @@ namespace {
 
 constexpr int kRows = 32;    // hidden units per workgroup
 constexpr int kChunk = 128;  // tokens per chunk
+constexpr float kNegLog2e = -1.4426950408889634f;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f32x16 mfma(const u32x4& a, const u32x4& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// A uniform value written before the launch, through the scalar cache: it does not join the
+// fragment loads' in-order wait.
+__device__ __forceinline__ float const_load(const float* p) {
+  return *(const __attribute__((address_space(4))) float*)p;
 }
 
 // This wave's LDS accesses are done; global loads stay in flight over the barrier.
@@ -65,6 +82,7 @@ __device__ __forceinline__ void step_wave(const SwStep& P, StepLds<NB, PAPER>& S
   constexpr int CA = CPW > 0 ? CPW : 1;  // array extents
   constexpr int KS = kChunk / 16;      // contraction steps over a chunk's tokens
   constexpr int PD = 4;                // phase 2 fragments are loaded PD steps ahead
+  constexpr int PF = NK < 10 ? NK : 10;  // phase 1 steps loaded before the phase starts
   unsigned char* const wts = S.wts;
   f32x4* const mlds = S.mom;
   float* const ssq = S.ssq;
@@ -92,12 +110,15 @@ __device__ __forceinline__ void step_wave(const SwStep& P, StepLds<NB, PAPER>& S
       for (int q = 0; q < 4; ++q) {
         const int c = chan(j, q);
         const bool ok = row_ok && c < dh;  // d_h is a multiple of 16
-        f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-        w[a][j][q] = ok ? *reinterpret_cast<const f32x4*>(wp[a] + wbase + c) : z;
+        // loads are unconditional (from the matrix's start where masked), so that all are in flight
+        const long long o = ok ? wbase + c : 0;
+        const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+        const f32x4 x = *reinterpret_cast<const f32x4*>(wp[a] + o);
+        w[a][j][q] = ok ? x : z;
         if constexpr (PAPER) {
-          const f32x4 x = ok ? *reinterpret_cast<const f32x4*>(mp[a] + wbase + c) : z;
-          if (a < ML) mlds[((a * MC + j) * 4 + q) * 256 + tid] = x;
-          else m[a - ML][j][q] = x;
+          const f32x4 y = *reinterpret_cast<const f32x4*>(mp[a] + o);
+          if (a < ML) mlds[((a * MC + j) * 4 + q) * 256 + tid] = ok ? y : z;
+          else m[a - ML][j][q] = ok ? y : z;
         }
       }
   float n0[3] = {0.0f, 0.0f, 0.0f};
@@ -144,8 +165,8 @@ __device__ __forceinline__ void step_wave(const SwStep& P, StepLds<NB, PAPER>& S
   auto frag = [&](const char* p, int i) { return *reinterpret_cast<const u32x4*>(p + voff + i * 1024); };
   // Fragments past the segment's tokens (up to the end of its last chunk, inside the buffers) are
   // finite leftovers of earlier segments; their products vanish with the exchange's zeros.
-  u32x4 kf[NK], yf[NK];
-  // phase 1 fragments [s0, s1) of this wave's tokens in chunk c of segment sg
+  u32x4 kf[PF], yf[PF];
+  // phase 1 fragments [s0, s1) of this wave's tokens in chunk c of segment sg (ring of PF steps)
   auto load1 = [&](int sg, int c, int s0, int s1) {
     const long long so = (long long)(4 * c + wave) * NK * 1024 + hb;
     const char* pk = reinterpret_cast<const char*>(P.kf + sg * P.k_ss) + so;
@@ -153,8 +174,8 @@ __device__ __forceinline__ void step_wave(const SwStep& P, StepLds<NB, PAPER>& S
 #pragma unroll
     for (int s = 0; s < NK; ++s) {
       if (s < s0 || s >= s1) continue;
-      kf[s] = frag(pk, s);
-      yf[s] = frag(py, s);
+      kf[s % PF] = frag(pk, s);
+      yf[s % PF] = frag(py, s);
     }
   };
   u32x4 kt[PD][CA], yt[PD][CA];
@@ -177,34 +198,39 @@ __device__ __forceinline__ void step_wave(const SwStep& P, StepLds<NB, PAPER>& S
   };
 
   load_rate(0, 0);
-  load1(0, 0, 0, NK);
+  load1(0, 0, 0, PF);
   int buf = 0;
   for (int sg = 0; sg < P.g; ++sg) {
     lds_barrier();  // the rows in LDS are those this segment starts from
-    float loss = 0.0f;
+    float loss = 0.0f, bt = 0.0f;
+    if constexpr (PAPER) bt = const_load(P.beta + sg * P.beta_ss + l);
     for (int c = 0; c < nch; ++c) {
       // ---- phase 1
       if (hf == 0) S.eta[wave][li] = etar;
       f32x16 sz, sgt, sd;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sz[r] = sgt[r] = sd[r] = 0.0f;
       auto wfrag = [&](int a, int s) {
         return *reinterpret_cast<const u32x4*>(wts + ((a * NK + s) * 64 + lane) * 16);
       };
-      // LDS fragments are read one step ahead; the scheduling barriers keep the compiler from
+      // LDS fragments are read AH steps ahead; the scheduling barriers keep the compiler from
       // hoisting later steps' reads (which would spill)
-      u32x4 bw[2][3];
+      constexpr int AH = 2;
+      const f32x16 zero = {};
+      u32x4 bw[AH + 1][3];
 #pragma unroll
-      for (int a = 0; a < 3; ++a) bw[0][a] = wfrag(a, 0);
+      for (int s = 0; s < AH; ++s)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) bw[s][a] = wfrag(a, s);
 #pragma unroll
       for (int s = 0; s < NK; ++s) {
-        if (s + 1 < NK) {
+        if (s + AH < NK) {
 #pragma unroll
-          for (int a = 0; a < 3; ++a) bw[(s + 1) & 1][a] = wfrag(a, s + 1);
+          for (int a = 0; a < 3; ++a) bw[(s + AH) % (AH + 1)][a] = wfrag(a, s + AH);
         }
-        sz = mfma(kf[s], bw[s & 1][0], sz);
-        sgt = mfma(kf[s], bw[s & 1][1], sgt);
-        sd = mfma(yf[s], bw[s & 1][2], sd);
+        const u32x4 (&bs)[3] = bw[s % (AH + 1)];
+        sz = mfma(kf[s % PF], bs[0], s ? sz : zero);
+        sgt = mfma(kf[s % PF], bs[1], s ? sgt : zero);
+        sd = mfma(yf[s % PF], bs[2], s ? sd : zero);
+        if (s + PF < NK) load1(sg, c, s + PF, s + PF + 1);
 #pragma unroll
         for (int p = (s * PD) / NK; p < ((s + 1) * PD) / NK; ++p) load2(sg, c, p);
         __builtin_amdgcn_sched_barrier(0);
@@ -212,6 +238,9 @@ __device__ __forceinline__ void step_wave(const SwStep& P, StepLds<NB, PAPER>& S
       // register r = 4 q + e: token 32 (4 c + wave) + 8 q + 4 hf + e, unit li
       unsigned char* ex = S.exch + buf * EXC;
       const int t0 = (4 * c + wave) * 32 + 4 * hf;
+      const bool last = c + 1 == nch;
+      // (after the last chunk: the first one again, never used)
+      const int sg_n = last ? (sg + 1 < P.g ? sg + 1 : 0) : sg, c_n = last ? 0 : c + 1;
       if ((4 * c + wave) * 32 + 32 > P.n) {  // tokens past the end contribute zeros
 #pragma unroll
         for (int r = 0; r < 16; ++r)
@@ -219,15 +248,17 @@ __device__ __forceinline__ void step_wave(const SwStep& P, StepLds<NB, PAPER>& S
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
+        if (q == 0) load_rate(sg_n, c_n);
+        load1(sg_n, c_n, (q * PF) / 4, ((q + 1) * PF) / 4);
         const f32x4 eta = *reinterpret_cast<const f32x4*>(&S.eta[wave][8 * q + 4 * hf]);
         float dz[4], dg[4], av[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float z = sz[4 * q + e], g = sgt[4 * q + e], da = sd[4 * q + e];
-          const float s = sigmoidf_(z);
+          const float s = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(kNegLog2e * z));
           const float si = z * s, a = si * g;
           const float eda = eta[e] * da;
-          dz[e] = eda * g * (s * (1.0f + z * (1.0f - s)));
+          dz[e] = eda * g * (s + si * (1.0f - s));  // SiLU'(z) = s (1 + z (1 - s))
           dg[e] = eda * si;
           av[e] = eta[e] * a;
           loss += a * da;
@@ -244,14 +275,10 @@ __device__ __forceinline__ void step_wave(const SwStep& P, StepLds<NB, PAPER>& S
       }
       lds_barrier();
       // ---- phase 2; the exchange alternates between two buffers, so one barrier per chunk
-      const bool last = c + 1 == nch;
-      // (after the last chunk: the first one again, never used)
-      const int sg_n = last ? (sg + 1 < P.g ? sg + 1 : 0) : sg, c_n = last ? 0 : c + 1;
       auto xfrag = [&](int a, int s) {
         return *reinterpret_cast<const u32x4*>(ex + a * kRows * kChunk * 2 +
                                                (li * 16 + ((2 * s + hf) ^ (li & 15))) * 16);
       };
-      load_rate(sg_n, c_n);
       u32x4 bx[2][3];
 #pragma unroll
       for (int a = 0; a < 3; ++a) bx[0][a] = xfrag(a, 0);
@@ -268,14 +295,12 @@ __device__ __forceinline__ void step_wave(const SwStep& P, StepLds<NB, PAPER>& S
           acc[2][j] = mfma(yt[s % PD][j], bx[s & 1][2], acc[2][j]);
         }
         if (s + PD < KS) load2(sg, c, s + PD);
-        load1(sg_n, c_n, (s * NK) / KS, ((s + 1) * NK) / KS);
         __builtin_amdgcn_sched_barrier(0);
       }
       buf ^= 1;
     }
     // ---- update: register 4 q + e of acc[a][j] is element e of w[a][j][q]
     float ss[3] = {0.0f, 0.0f, 0.0f};
-    const float bt = PAPER ? P.beta[sg * P.beta_ss + l] : 0.0f;
 #pragma unroll
     for (int a = 0; a < 3; ++a)
 #pragma unroll
@@ -324,9 +349,11 @@ __device__ __forceinline__ void step_wave(const SwStep& P, StepLds<NB, PAPER>& S
       }
     }
     put_weights();
+    if (sg + 1 == P.g) {  // the last segment's loss is the one reported
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off, 64);
-    if (lane == 0) P.loss_part[(long long)b * P.parts + rb * 4 + wave] = loss;
+      for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off, 64);
+      if (lane == 0) P.loss_part[(long long)b * P.parts + rb * 4 + wave] = loss;
+    }
   }
 #pragma unroll
   for (int a = 0; a < 3; ++a)

@@ -503,3 +503,45 @@ def test_segments_overlapped_batches_bitwise(act, optimizer):
     torch.cuda.synchronize()
     same()
     _check(a, range(cfg.n_layers), 1e-4 if act == "f32" else 2e-2, 1e-4 if act == "f32" else 1e-2)
+
+
+# ------------------------------------------------------------------------------------------
+# The one-kernel memory step (bf16): chunks of 128 tokens in blocks of 32, 32 hidden units per
+# workgroup, channel blocks of 32 over 4 waves.  Bars as above.
+
+@pytest.mark.parametrize("optimizer", ["sgd", "paper"])
+@pytest.mark.parametrize("n_heads,d_head,ns", [
+    (4, 16, (300, 1, 129)),     # half a channel block and half a block of hidden units
+    (4, 48, (64, 33, 300)),     # the second block half padding
+    (2, 160, (128, 127, 31)),   # 5 blocks: one wave with two
+    (4, 240, (257, 32, 96)),    # 8 blocks, the last half padding
+    (1, 256, (300, 128, 65)),   # the widest head
+])
+def test_bf16_step_edges(n_heads, d_head, ns, optimizer):
+    cfg = configs.SwigluConfig(f"sw_step{d_head}_{optimizer}", n_layers=2,
+                               d_model=n_heads * d_head, n_heads=n_heads, d_head=d_head,
+                               seg_len=300, n_context=900, act_dtype="bf16", lr=2.0,
+                               optimizer=optimizer)
+    p = SwProblem(cfg)
+    for s, n in enumerate(ns):
+        p.segment(s, n)
+    _check(p, range(cfg.n_layers), 2e-2, 1e-2)
+
+
+@pytest.mark.parametrize("optimizer", ["sgd", "paper"])
+def test_bf16_step_batches_of_192_token_segments(optimizer):
+    """Segments that end inside a chunk, several per launch: bitwise one call per segment."""
+    cfg = configs.SwigluConfig(f"sw_b192_{optimizer}", n_layers=3, d_model=448, n_heads=2,
+                               d_head=224, seg_len=192, n_context=1920, act_dtype="bf16", lr=1.0,
+                               optimizer=optimizer, prep_segments=4)
+    a, b = SwProblem(cfg), SwProblem(cfg)
+    a.segments(0, 9)
+    for s in range(9):
+        b.segment(s, cfg.seg_len)
+    torch.cuda.synchronize()
+    for m in range(3):
+        assert torch.equal(a.w[m], b.w[m]), m
+        if optimizer == "paper":
+            assert torch.equal(a.mom[m], b.mom[m]), m
+    assert np.array_equal(a.sess.loss(), b.sess.loss())
+    _check(a, range(cfg.n_layers), 2e-2, 1e-2)
