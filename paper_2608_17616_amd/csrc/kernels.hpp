@@ -750,6 +750,8 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
             stw[sidx(ii * 32 + g * 8 + (lane >> 5) * 4 + e, jj * 32 + (lane & 31))] =
                 acc[2 * sm + ii][2 * sn + jj][4 * g + e];
     wave_sync();
+    [[maybe_unused]] typename Epi::Blk blk;
+    if constexpr (Epi::kBlk) blk = G.epi.block(layer, grow, gcol, cq);
     if constexpr (Epi::kPre && !Epi::kPreLate) {
       if (sb + 1 < NSB && !pack_all) issue_pre(sb + 1, aux[(sb + 1) & 1]);
     }
@@ -781,7 +783,9 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
         if (ok) val = G.epi.rows8p(pi, layer, grow + r, gcol + c, P.M, P.N, v, w, aux[sb & 1][b]);
         partial += val;
       } else if (ok) {
-        if (pack_all) {
+        if constexpr (Epi::kBlk) {
+          val = G.epi.rows8(blk, r, v);
+        } else if (pack_all) {
           float x[NAUX];
           const float* w = &aux[sb >> 1][b][4 * (sb & 1)];
 #pragma unroll
@@ -825,7 +829,9 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
       if (sb + 1 < NSB && !pack_all) issue_pre(sb + 1, aux[(sb + 1) & 1]);
     }
     if constexpr (Epi::kCols) {
-      if (G.epi.has_cols(pi)) {
+      bool cols = G.epi.has_cols(pi);
+      if constexpr (Epi::kBlk) cols = blk.cols;
+      if (cols) {
         if constexpr (Epi::kWriteback) wave_sync();
         const int kc = lane & 7;  // row group of this lane's column chunks
 #pragma unroll
@@ -835,7 +841,8 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
           float v[8];
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] = stw[sidx(8 * kc + e, c)];
-          G.epi.cols8(pi, layer, grow + 8 * kc, gcol + c, P.M, P.N, v);
+          if constexpr (Epi::kBlk) G.epi.cols8(blk, 8 * kc, c, v);
+          else G.epi.cols8(pi, layer, grow + 8 * kc, gcol + c, P.M, P.N, v);
         }
       }
     }
@@ -889,6 +896,12 @@ struct EpiBase {
   __device__ __forceinline__ void row_partial(int, int, int, int, float) const {}
   static constexpr bool kCols = false;
   static constexpr bool kWriteback = false;
+  // kBlk: block() computes once per lane and 64 x 64 sub-block (rows grow.., columns gcol.., this
+  // lane's row chunks at column gcol + cq) what its chunks share (addresses, per-channel factors),
+  // and rows8(blk, row in the sub-block, v), cols8(blk, row, column, v) take the place of the
+  // forms above; blk.cols: the sub-block has a column pass
+  struct Blk {};
+  static constexpr bool kBlk = false;
   __device__ __forceinline__ bool has_cols(int) const { return false; }
   // part 0 of a K-concatenated contraction contributes part0_scale(layer, col) times its
   // product to column col (when has_part0_scale())

@@ -258,6 +258,7 @@ int run_sw_prep(mone_swiglu* H, const void* x, long long lsx, int n, int g, int 
     epi.d = d; epi.dh = dh; epi.dhp = dhp; epi.H = NH; epi.Tp = Tp; epi.n = n;
     epi.seg_rows = seg_rows; epi.kpre_rows = kpre_rows;
     epi.dy_ss = Ly.dy_ss; epi.dyt_ss = Ly.dyt_ss; epi.rate_ss = Ly.rate_ss;
+    epi.inv_dh = 1.0f / (float)dh; epi.inv_seg = 1.0f / (float)seg_rows;
     H->timer.begin(MONE_SW_STAGE_PROJ, s);
     // 128 x 128 tiles (measured faster here than 256 x 256, which leave most CUs idle in
     // their second round); 64-row tiles for short segments

@@ -50,56 +50,100 @@ struct EpiSwProj : EpiBase {
   int d, dh, dhp, H, Tp, n;
   int seg_rows, kpre_rows;
   long long dy_ss, dyt_ss, rate_ss;
+  // What a chunk's address needs (its segment, its head) is found once per sub-block: the integer
+  // divisions per chunk and the reloaded scales were half of the epilogue's instructions, which
+  // with two workgroups per CU took about as long as the 14-step main loop.  8 segments at 24
+  // layers of 896: 587 -> 507 us a launch.
+  float inv_dh, inv_seg;  // 1 / d_h, 1 / seg_rows
   static constexpr bool kFrag = sizeof(E) == 2;
+  static constexpr bool kBlk = true;
+  // Quotient of 0 <= a < 2^22 by b through inv = 1 / b: (a + 1/2) / b is at least 1 / (2 b) away
+  // from an integer, more than the products' rounding error (a / b) 2^-22.
+  static __device__ __forceinline__ int quot(int a, float inv) {
+    return (int)(((float)a + 0.5f) * inv);
+  }
   __device__ __forceinline__ bool has_cols(int) const { return true; }
-  __device__ __forceinline__ float rows8(int, int l, int row, int col, int, int, float (&v)[8],
-                                         const float (&)[8]) const {
-    const int sg = row / seg_rows, t = row - sg * seg_rows;
+  // Rows of a 64-row sub-block are one segment's (seg_rows is a multiple of 64), its columns all
+  // keys or all values (d is a multiple of 64).
+  struct Blk {
+    bool key, cols;
+    int l, gc;          // layer; first value column of the sub-block
+    int t0, nv;         // token of the first row, rows with a token (t < n)
+    E* p;               // output of the lane's row chunks at row 0
+    const float* rate;  // fp32 values: the rates at row 0, or null
+    E* yt;              // values: this segment's channel-major dY
+    float sc[8], sh[8];  // keys: scale and shift of the lane's 8 channels
+  };
+  __device__ __forceinline__ Blk block(int l, int grow, int gcol, int cq) const {
+    Blk k;
+    grow = __builtin_amdgcn_readfirstlane(grow);
+    gcol = __builtin_amdgcn_readfirstlane(gcol);
+    const int sg = quot(grow, inv_seg), col = gcol + cq;
+    k.l = l;
+    k.t0 = grow - sg * seg_rows;
+    k.nv = n - k.t0;
+    k.key = gcol < d;
+    k.cols = !k.key;
+    k.gc = gcol - d;
+    k.rate = nullptr;
+    k.yt = dyt + sg * dyt_ss;
+    if (k.key) {
+      const int c = col < d ? col : 0;
+      load8(kscale + (long long)l * d + c, k.sc);
+      load8(kshift + (long long)l * d + c, k.sh);
+      k.p = kpre + ((long long)l * kpre_rows + (long long)sg * Tp + k.t0) * d + col;
+    } else {
+      const int c = col - d, e = quot(c, inv_dh), ch = c - e * dh;
+      if constexpr (kFrag)
+        k.p = dy + sg * dy_ss + tok_frag(l * H + e, k.t0, ch, Tp, dh);
+      else
+        k.p = dy + sg * dy_ss + (((long long)l * H + e) * Tp + k.t0) * dhp + ch;
+      if (!kFrag && rate) k.rate = rate + sg * rate_ss + (long long)l * Tp + k.t0;
+    }
+    return k;
+  }
+  __device__ __forceinline__ float rows8(const Blk& k, int r, float (&v)[8]) const {
     float o[8];
-    if (col < d) {
-      const float* sc = kscale + (long long)l * d + col;
-      const float* sh = kshift + (long long)l * d + col;
+    const bool ok = r < k.nv;
+    if (k.key) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        const float u = sc[e] * v[e] + sh[e];
-        o[e] = t < n ? u * sigmoidf_(u) : 0.0f;
+        const float u = k.sc[e] * v[e] + k.sh[e];
+        o[e] = u * sigmoidf_(u);
       }
-      store8(kpre + ((long long)l * kpre_rows + (long long)sg * Tp + t) * d + col, o);
+      if (!ok) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = 0.0f;
+      }
+      store8(k.p + r * d, o);
     } else {
-      const int c = col - d, e = c / dh, ch = c - e * dh;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const float sv = t < n ? v[i] * sigmoidf_(v[i]) : 0.0f;
-        v[i] = sv;
+        const float sv = v[i] * sigmoidf_(v[i]);
         o[i] = -sv * inv_n;
+        v[i] = kFrag ? o[i] : sv;
+      }
+      if (!ok) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] = v[i] = 0.0f;
       }
       if constexpr (kFrag)
-        store8(dy + sg * dy_ss + tok_frag(l * H + e, t, ch, Tp, dh), o);
+        store8(k.p + ((r >> 5) * 2 * ((dh + 31) >> 5) * 512 + (r & 31) * 8), o);
       else
-        store8(dy + sg * dy_ss + (((long long)l * H + e) * Tp + t) * dhp + ch, o);
+        store8(k.p + r * dhp, o);
     }
     return 0.0f;
   }
-  __device__ __forceinline__ void cols8(int, int l, int row, int col, int, int,
-                                        const float (&v)[8]) const {
-    if (col < d) return;
-    const int sg = row / seg_rows, t = row - sg * seg_rows;
-    const int c = col - d, e = c / dh, ch = c - e * dh;
+  __device__ __forceinline__ void cols8(const Blk& k, int r, int c, const float (&v)[8]) const {
+    const int e = quot(k.gc + c, inv_dh), ch = k.gc + c - e * dh, t = k.t0 + r;
     if constexpr (kFrag) {
+      store8(k.yt + chan_frag(k.l * H + e, t, ch, Tp, dh), v);
+    } else {
       float o[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) o[i] = -v[i] * inv_n;
-      store8(dyt + sg * dyt_ss + chan_frag(l * H + e, t, ch, Tp, dh), o);
-      return;
+      for (int i = 0; i < 8; ++i) o[i] = -(k.rate ? k.rate[r + i] : lr) * v[i] * inv_n;
+      store8(k.yt + (((long long)k.l * H + e) * dh + ch) * Tp + t, o);
     }
-    const float* rt = rate ? rate + sg * rate_ss + (long long)l * Tp + t : nullptr;
-    float o[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float eta = rt ? rt[i] : lr;
-      o[i] = -eta * v[i] * inv_n;
-    }
-    store8(dyt + sg * dyt_ss + (((long long)l * H + e) * dh + ch) * Tp + t, o);
   }
 };
 
