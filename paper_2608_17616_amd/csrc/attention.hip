@@ -1,0 +1,479 @@
+// Memory injection into attention for gfx950: causal softmax attention of the query tokens over
+// their own keys and the memory's keys, one softmax over both sets.
+//
+//   out[i] = softmax over j <= i of [ scale q_i . k_j , scale q_i . km_j ] applied to [v_j ; vm_j]
+//
+// A workgroup takes up to 4 pairs (query head, block of 32 query rows) of one key/value head and
+// layer, one per wave (heads of a group side by side, so that grouped queries share the staged
+// keys), and visits the positions in chunks of 32 of both sets.  All products run on the matrix
+// cores in bf16 with fp32 accumulation and no loss of precision:
+//   - bf16 operands are used as they are; fp32 operands are staged as three bf16 planes that sum
+//     to them exactly (8 + 8 + 8 bits, by truncation), and so are the fp32 probabilities;
+//   - products of planes whose weights together lie below 2^-24 of the result's are left out
+//     (three of nine), the others accumulate in fp32.
+// S^T = K Q^T puts a lane's 16 scores in one query column, so the softmax is in-lane sums and one
+// exchange between lanes l and l + 32, and P^T is the B operand of O^T = V^T P^T straight from
+// registers: the contraction's key order inside a 16-key step is permuted (0-3, 8-11, 4-7, 12-15),
+// and the staging of V^T in LDS uses the same order.
+//
+// Measured against one row per quarter wave with fp32 vector arithmetic from LDS: 32 layers, 32 / 8
+// heads of 128, 64 rows, fp32 memory rows 255 -> 25 us; 16 layers, 32 / 8 heads of 64, 512 rows, all
+// bf16 4720 -> 154 us; the error against 64 bits 1.9e-7 -> 1.5e-7 (fp32 out).  What bounds it: the
+// short batch its bytes and one pass of latencies (two workgroups per CU), the long one the
+// elementwise part (splitting the probabilities, exponentials) beside 8 to 24 MFMAs per 32 x 32
+// scores.
+#include "attention.hpp"
+
+#include <math.h>
+
+#include "kernels.hpp"
+
+namespace mone {
+namespace {
+
+constexpr int kKeys = 32;   // positions per chunk (of each set)
+constexpr int kRowsW = 32;  // query rows per wave
+
+__device__ __forceinline__ f32x16 mfma_bf16(const u32x4& a, const u32x4& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Upper halves of two floats, a's in the low 16 bits.
+__device__ __forceinline__ uint32_t hi_pair(float a, float b) {
+  return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);
+}
+__device__ __forceinline__ float trunc_bf16(float x) {
+  return __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+}
+
+// Planes of two floats: p[0] + p[1] + p[2] = the values, exactly.  FINITE: the inputs are known
+// to be finite or a quiet NaN; otherwise an infinity keeps zero lower planes (inf - inf) and a NaN
+// stays one in the first plane.
+template <bool FINITE>
+__device__ __forceinline__ void split3(float a, float b, uint32_t (&p)[3]) {
+  if constexpr (!FINITE) {
+    a = a != a ? __builtin_nanf("") : a;
+    b = b != b ? __builtin_nanf("") : b;
+  }
+  p[0] = hi_pair(a, b);
+  float ra = a - trunc_bf16(a), rb = b - trunc_bf16(b);
+  if constexpr (!FINITE) {
+    ra = ra != ra ? 0.0f : ra;
+    rb = rb != rb ? 0.0f : rb;
+  }
+  p[1] = hi_pair(ra, rb);
+  p[2] = hi_pair(ra - trunc_bf16(ra), rb - trunc_bf16(rb));
+}
+
+// Eight consecutive elements of one row as loaded.
+template <typename T>
+struct Raw8 {
+  u32x4 v[sizeof(T) / 2];
+};
+
+// Elements c .. c+7 of a row of dh columns (zero at or past dh, or where !ok); VEC: dh is a
+// multiple of 8 and rows are 16-byte aligned.
+template <typename T, bool VEC>
+__device__ __forceinline__ Raw8<T> load_raw(const T* row, int c, int dh, bool ok) {
+  Raw8<T> r;
+#pragma unroll
+  for (int i = 0; i < (int)sizeof(T) / 2; ++i) r.v[i] = u32x4{0, 0, 0, 0};
+  if constexpr (VEC) {
+    if (ok && c < dh) {
+#pragma unroll
+      for (int i = 0; i < (int)sizeof(T) / 2; ++i)
+        r.v[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(row + c) + 16 * i);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if (!ok || c + e >= dh) continue;
+      if constexpr (sizeof(T) == 2)
+        r.v[0][e >> 1] |= (uint32_t)row[c + e] << (16 * (e & 1));
+      else
+        r.v[e >> 2][e & 3] = __float_as_uint(row[c + e]);
+    }
+  }
+  return r;
+}
+
+// Plane p of a raw row piece, as 8 packed bf16.
+template <typename T, int NP>
+__device__ __forceinline__ void planes(const Raw8<T>& r, u32x4 (&p)[NP]) {
+  if constexpr (sizeof(T) == 2) {
+    p[0] = r.v[0];
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t w[3];
+      split3<false>(__uint_as_float(r.v[i >> 1][(2 * i) & 3]),
+                    __uint_as_float(r.v[i >> 1][(2 * i + 1) & 3]), w);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) p[k][i] = w[k];
+    }
+  }
+}
+
+// E: activations (queries, keys, values), EM: memory rows; DHP: head width padded to a multiple of
+// 32 (zero columns); VEC: dh a multiple of 8.
+template <typename E, typename EM, int DHP, bool VEC>
+__global__ __launch_bounds__(256, DHP > 128 || (DHP == 128 && sizeof(E) == 4) ? 1 : 2) void attention_kernel(Attention P) {
+  constexpr int QP = sizeof(E) == 2 ? 1 : 3, MP = sizeof(EM) == 2 ? 1 : 3;
+  constexpr int NS = DHP / 16;   // contraction steps over the head's channels
+  constexpr int NB = DHP / 32;   // blocks of output columns
+  constexpr int PLANE = kKeys * DHP * 2;  // bytes of one plane of one set's keys (or values)
+  constexpr int KV = (QP + MP) * PLANE;
+  // keys and values in separate buffers where they fit, else one after the other in one
+  constexpr bool SEP = 2 * KV <= 80 * 1024;
+  // the next chunk's rows are loaded during this one's products (register room)
+  constexpr bool AHEAD = DHP <= 128;
+  constexpr int UK = (4 * DHP + 255) / 256;  // 8-channel pieces of a set's keys per thread
+  constexpr int UV = (2 * DHP + 255) / 256;  // ... pairs of rows of its values per thread
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[SEP ? 2 * KV : KV];
+  unsigned char* const ks = smem;
+  unsigned char* const vs = SEP ? smem + KV : smem;
+
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l = blockIdx.z, g = blockIdx.y, q = P.q, dh = P.dh;
+  const int gs = P.n_heads / P.n_kv_heads, nblk = (q + kRowsW - 1) / kRowsW, npair = gs * nblk;
+  const int p0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * 4;  // the longest rows first
+  const int pw = p0 + wave, pl = p0 + 3 < npair ? p0 + 3 : npair - 1;
+  const int nch = pl / gs + 1;                 // chunks of this workgroup
+  const int pb = pw < npair ? pw / gs : -1;    // this wave's block of query rows (-1: none)
+  const int a = g * gs + (pw < npair ? pw % gs : 0);
+  const int i = pb * kRowsW + li;              // this lane's query row
+  const int lim = i < q ? i : q - 1;           // last position it sees (rows past q: not stored)
+
+  const long long qw = (long long)P.n_heads * dh, kw = (long long)P.n_kv_heads * dh;
+  const E* ql = reinterpret_cast<const E*>(P.qh) + (long long)l * q * qw + (long long)a * dh;
+  const E* kl = reinterpret_cast<const E*>(P.kh) + (long long)l * q * kw + (long long)g * dh;
+  const E* vl = reinterpret_cast<const E*>(P.vh) + (long long)l * q * kw + (long long)g * dh;
+  const EM* ml = reinterpret_cast<const EM*>(P.kv_mem) + (long long)l * q * 2 * P.d_kv +
+                 (long long)g * dh;
+
+  // queries as B fragments: channels 16 s + 8 hf .. of row i
+  u32x4 qf[NS][QP];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const Raw8<E> r =
+        load_raw<E, VEC>(ql + (long long)(i < 0 ? 0 : lim) * qw, 16 * s + 8 * hf, dh, pb >= 0);
+    planes<E, QP>(r, qf[s]);
+  }
+
+  Raw8<E> rk0[UK], rv0[UV][2];
+  Raw8<EM> rk1[UK], rv1[UV][2];
+  auto load_keys = [&](int j0) {
+#pragma unroll
+    for (int u = 0; u < UK; ++u) {
+      const int x = tid + 256 * u, key = x / (DHP / 8), c = (x % (DHP / 8)) * 8, j = j0 + key;
+      const bool ok = key < kKeys && j < q;
+      rk0[u] = load_raw<E, VEC>(kl + (long long)(ok ? j : 0) * kw, c, dh, ok);
+      rk1[u] = load_raw<EM, VEC>(ml + (long long)(ok ? j : 0) * 2 * P.d_kv, c, dh, ok);
+    }
+  };
+  auto load_values = [&](int j0) {
+#pragma unroll
+    for (int u = 0; u < UV; ++u) {
+      const int x = tid + 256 * u, kp = x / (DHP / 8), c = (x % (DHP / 8)) * 8;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int j = j0 + 2 * kp + k;
+        const bool ok = 2 * kp < kKeys && j < q;
+        rv0[u][k] = load_raw<E, VEC>(vl + (long long)(ok ? j : 0) * kw, c, dh, ok);
+        rv1[u][k] = load_raw<EM, VEC>(ml + (long long)(ok ? j : 0) * 2 * P.d_kv + P.d_kv, c, dh, ok);
+      }
+    }
+  };
+  // keys as A fragments [plane][NS][64 x 16 bytes]: channels 8 c8 .. of key k in slot
+  // (c8 & 1) * 32 + (k ^ (c8 & 7)) of fragment c8 / 2 (the exchange spreads the banks of a row's
+  // stores); set 0's planes, then set 1's
+  auto put_key = [&](auto np, int base, const auto& raw, int u) {
+    constexpr int NP = decltype(np)::value;
+    const int x = tid + 256 * u, key = x / (DHP / 8), c8 = x % (DHP / 8);
+    if (key >= kKeys) return;
+    u32x4 p[NP];
+    planes(raw, p);
+#pragma unroll
+    for (int k = 0; k < NP; ++k)
+      *reinterpret_cast<u32x4*>(ks + base + k * PLANE + (c8 >> 1) * 1024 +
+                                ((c8 & 1) * 32 + (key ^ (c8 & 7))) * 16) = p[k];
+  };
+  // values as A fragments of V^T [plane][NB][2][64 x 16 bytes]: column c, key k of a 16-key step:
+  // half (k >> 2) & 1, position (k & 3) + 4 (k >> 3); the column's slot exchanged within 8
+  auto put_value = [&](auto np, int base, const auto& raw, int u) {
+    constexpr int NP = decltype(np)::value;
+    const int x = tid + 256 * u, kp = x / (DHP / 8), c8 = x % (DHP / 8);
+    if (2 * kp >= kKeys) return;
+    u32x4 p0v[NP], p1v[NP];
+    planes(raw[0], p0v);
+    planes(raw[1], p1v);
+    const int kk = (2 * kp) & 15;
+    const int at = (((c8 >> 2) * 2 + (kp >> 3)) * 64 + ((kk >> 2) & 1) * 32) * 16 +
+                   ((kk & 3) + 4 * (kk >> 3)) * 2;
+#pragma unroll
+    for (int k = 0; k < NP; ++k)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int c = (c8 & 3) * 8 + (e ^ ((2 * (c8 & 3)) & 7));
+        const uint32_t x0 = p0v[k][e >> 1], x1 = p1v[k][e >> 1];
+        *reinterpret_cast<uint32_t*>(vs + base + k * PLANE + at + c * 16) =
+            e & 1 ? (x0 >> 16) | (x1 & 0xffff0000u) : (x0 & 0xffffu) | (x1 << 16);
+      }
+  };
+  using QPc = std::integral_constant<int, QP>;
+  using MPc = std::integral_constant<int, MP>;
+  auto put_keys = [&] {
+#pragma unroll
+    for (int u = 0; u < UK; ++u) {
+      put_key(QPc{}, 0, rk0[u], u);
+      put_key(MPc{}, QP * PLANE, rk1[u], u);
+    }
+  };
+  auto put_values = [&] {
+#pragma unroll
+    for (int u = 0; u < UV; ++u) {
+      put_value(QPc{}, 0, rv0[u], u);
+      put_value(MPc{}, QP * PLANE, rv1[u], u);
+    }
+  };
+
+  f32x16 o[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[b][r] = 0.0f;
+  float m = -INFINITY, lsum = 0.0f;
+
+  // scores of one set (keys' planes from `base`)
+  auto scores = [&](auto np, int base) {
+    constexpr int NP = decltype(np)::value;
+    f32x16 sc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sc[r] = 0.0f;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int c8 = 2 * s + hf;
+#pragma unroll
+      for (int k = NP - 1; k >= 0; --k) {
+        const u32x4 kf = *reinterpret_cast<const u32x4*>(
+            ks + base + k * PLANE + s * 1024 + (hf * 32 + (li ^ (c8 & 7))) * 16);
+#pragma unroll
+        for (int t = QP - 1; t >= 0; --t)
+          if (k + t < 3) sc = mfma_bf16(kf, qf[s][t], sc);
+      }
+    }
+    return sc;
+  };
+  // o += the set's values times its probabilities (register 4 q + e: key 8 q + 4 hf + e)
+  auto weigh = [&](auto np, int base, const float (&p)[16]) {
+    constexpr int NP = decltype(np)::value;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      u32x4 pf[3];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        uint32_t x[3];
+        split3<true>(p[8 * t + 2 * w], p[8 * t + 2 * w + 1], x);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) pf[k][w] = x[k];
+      }
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int k = NP - 1; k >= 0; --k) {
+          const int c = (li & 24) | ((li ^ (2 * (li >> 3))) & 7);
+          const u32x4 vf = *reinterpret_cast<const u32x4*>(
+              vs + base + k * PLANE + ((b * 2 + t) * 64 + hf * 32 + c) * 16);
+#pragma unroll
+          for (int x = 2; x >= 0; --x)
+            if (k + x < 3) o[b] = mfma_bf16(vf, pf[x], o[b]);
+        }
+    }
+  };
+
+  if (AHEAD) {
+    load_keys(0);
+    load_values(0);
+  }
+  for (int ch = 0; ch < nch; ++ch) {
+    const int j0 = ch * kKeys;
+    if (!AHEAD) load_keys(j0);
+    lds_barrier();  // the previous chunk is consumed
+    put_keys();
+    if (SEP) {
+      if (!AHEAD) load_values(j0);
+      put_values();
+    }
+    lds_barrier();
+    const bool mine = ch <= pb;
+    if (AHEAD && ch + 1 < nch) {
+      if (SEP) {
+        load_keys(j0 + kKeys);
+        load_values(j0 + kKeys);
+      } else {
+        load_keys(j0 + kKeys);
+      }
+    }
+    float pr[2][16];
+    if (mine) {
+      const f32x16 s0 = scores(QPc{}, 0), s1 = scores(MPc{}, QP * PLANE);
+      float mx = m;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const bool ok = j0 + 8 * (r >> 2) + 4 * hf + (r & 3) <= lim;
+        pr[0][r] = ok ? s0[r] * P.scale : -INFINITY;
+        pr[1][r] = ok ? s1[r] * P.scale : -INFINITY;
+        mx = fmaxf(mx, fmaxf(pr[0][r], pr[1][r]));
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));  // finite: position 0 is in every row's first chunk
+      const float c = __expf(m - mx);
+      float ps = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          pr[k][r] = __expf(pr[k][r] - mx);
+          ps += pr[k][r];
+        }
+      ps += __shfl_xor(ps, 32, 64);
+      lsum = lsum * c + ps;
+      m = mx;
+      if (__any(c != 1.0f)) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[b][r] *= c;
+      }
+    }
+    if (!SEP) {
+      if (!AHEAD) load_values(j0);
+      lds_barrier();  // the keys are consumed: the values take their place
+      put_values();
+      lds_barrier();
+      if (AHEAD && ch + 1 < nch) load_values(j0 + kKeys);
+    }
+    if (mine) {
+      weigh(QPc{}, 0, pr[0]);
+      weigh(MPc{}, QP * PLANE, pr[1]);
+    }
+  }
+  if (pb < 0) return;
+  const long long ob = ((long long)l * q + i) * qw + (long long)a * dh;
+  // A NaN may only be an infinite operand's product with a zero plane of the other one: such a
+  // wave's rows are computed again, element by element in fp32.  Lanes l and l + 32 share a row:
+  // each forms one set's scores and half of the columns.
+  float nan = lsum;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) nan += o[b][r] * 0.0f;
+  if (__any(nan != nan)) {
+    auto score = [&](int j) {
+      float s = 0.0f;
+      const E* qi = ql + (long long)lim * qw;
+      if (hf == 0) {
+        for (int c = 0; c < dh; ++c) s += to_f32(qi[c]) * to_f32(kl[(long long)j * kw + c]);
+      } else {
+        for (int c = 0; c < dh; ++c)
+          s += to_f32(qi[c]) * to_f32(ml[(long long)j * 2 * P.d_kv + c]);
+      }
+      return s * P.scale;
+    };
+    float mx = -INFINITY, sum = 0.0f;
+    for (int j = 0; j <= lim; ++j) mx = fmaxf(mx, score(j));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    for (int j = 0; j <= lim; ++j) sum += __expf(score(j) - mx);
+    const float other = __shfl_xor(sum, 32, 64);
+    const float is = 1.0f / (hf == 0 ? sum + other : other + sum);
+    for (int b = 0; b < NB; ++b) {
+      float acc[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+      // both lanes of a row run the same positions (they exchange their probabilities)
+      for (int j = 0; j <= lim; ++j) {
+        const float p = __expf(score(j) - mx), po = __shfl_xor(p, 32, 64);
+        const float pq = hf == 0 ? p : po, pm = hf == 0 ? po : p;
+        const E* vj = vl + (long long)j * kw;
+        const EM* mj = ml + (long long)j * 2 * P.d_kv + P.d_kv;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int c = 32 * b + 8 * (r >> 2) + 4 * hf + (r & 3);
+          if (c < dh) acc[r] += pq * to_f32(vj[c]) + pm * to_f32(mj[c]);
+        }
+      }
+      if (i < q) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int c = 32 * b + 8 * (r >> 2) + 4 * hf + (r & 3);
+          if (c >= dh) continue;
+          if (P.out_bf16) reinterpret_cast<bf16_t*>(P.out)[ob + c] = from_f32<bf16_t>(acc[r] * is);
+          else reinterpret_cast<float*>(P.out)[ob + c] = acc[r] * is;
+        }
+      }
+    }
+    return;
+  }
+  if (i >= q) return;
+  const float inv = 1.0f / lsum;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int c = 32 * b + 8 * x + 4 * hf;
+      float v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = o[b][4 * x + e] * inv;
+      if (VEC) {
+        if (c >= dh) continue;
+        if (P.out_bf16) {
+          uint2 w;
+          w.x = pack_bf16(v[0], v[1]);
+          w.y = pack_bf16(v[2], v[3]);
+          *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(P.out) + ob + c) = w;
+        } else {
+          *reinterpret_cast<float4*>(reinterpret_cast<float*>(P.out) + ob + c) =
+              make_float4(v[0], v[1], v[2], v[3]);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (c + e >= dh) continue;
+          if (P.out_bf16) reinterpret_cast<bf16_t*>(P.out)[ob + c + e] = from_f32<bf16_t>(v[e]);
+          else reinterpret_cast<float*>(P.out)[ob + c + e] = v[e];
+        }
+      }
+    }
+}
+
+template <typename E, typename EM, int DHP>
+void launch_width(const Attention& a, hipStream_t s) {
+  const int pairs = (a.n_heads / a.n_kv_heads) * ((a.q + kRowsW - 1) / kRowsW);
+  const dim3 grid((unsigned)((pairs + 3) / 4), (unsigned)a.n_kv_heads, (unsigned)a.L), block(256);
+  if (a.dh % 8 == 0) attention_kernel<E, EM, DHP, true><<<grid, block, 0, s>>>(a);
+  else attention_kernel<E, EM, DHP, false><<<grid, block, 0, s>>>(a);
+}
+
+template <typename E, typename EM>
+void launch_types(const Attention& a, hipStream_t s) {
+  if (a.dh <= 32) launch_width<E, EM, 32>(a, s);
+  else if (a.dh <= 64) launch_width<E, EM, 64>(a, s);
+  else if (a.dh <= 128) launch_width<E, EM, 128>(a, s);
+  else launch_width<E, EM, 256>(a, s);
+}
+
+}  // namespace
+
+hipError_t launch_attention_kernel(const Attention& a, hipStream_t s) {
+  if (a.act_bf16) {
+    if (a.mem_bf16) launch_types<bf16_t, bf16_t>(a, s);
+    else launch_types<bf16_t, float>(a, s);
+  } else {
+    if (a.mem_bf16) launch_types<float, bf16_t>(a, s);
+    else launch_types<float, float>(a, s);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace mone

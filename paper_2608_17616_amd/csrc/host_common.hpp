@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "../../include/mone_ttl.h"
+#include "attention.hpp"
 #include "kernels.hpp"
 
 // Message of the last failing call on this thread (defined once, in mone_ttl.hip).
@@ -192,9 +193,8 @@ hipError_t launch_gemm(TileShape t, const Spec* specs, int nspec, int layers, co
   }
 }
 
-// Memory injection into attention (Eq. attn with Eq. std_attn): validation and the launch of
-// memory_attention_kernel for L layers of K/V width d_kv; 16 query rows per workgroup.  With
-// q = 0 nothing is launched.
+// Memory injection into attention (Eq. attn with Eq. std_attn): validation and the launch, for L
+// layers of K/V width d_kv.  With q = 0 nothing is launched.
 inline int launch_attention(int L, int d_kv, bool act_bf16, const void* qh, const void* kh,
                             const void* vh, const void* kv_mem, int kv_dtype, int q, int n_heads,
                             int n_kv_heads, void* out, int out_dtype, hipStream_t s) {
@@ -212,31 +212,14 @@ inline int launch_attention(int L, int d_kv, bool act_bf16, const void* qh, cons
     return fail(MONE_EINVAL, "qh, kh, vh, kv_mem and out must be non-NULL");
   if (!aligned16(qh) || !aligned16(kh) || !aligned16(vh) || !aligned16(kv_mem) || !aligned16(out))
     return fail(MONE_EINVAL, "qh, kh, vh, kv_mem and out must be 16-byte aligned");
-  const dim3 grid((q + 15) / 16, n_heads, L), block(256);
-  const float scale = 1.0f / std::sqrt((float)dh);
-  const bool kbf = kv_dtype == MONE_BF16, obf = out_dtype == MONE_BF16;
-  // the eight dtype combinations of (activations, memory K/V, output), for heads of up to 128
-  // columns or up to 256
-#define MONE_ATTN_W(EA, EK, EO, DHM)                                                            \
-  memory_attention_kernel<EA, EK, EO, DHM><<<grid, block, 0, s>>>(                             \
-      reinterpret_cast<const EA*>(qh), reinterpret_cast<const EA*>(kh),                         \
-      reinterpret_cast<const EA*>(vh), reinterpret_cast<const EK*>(kv_mem),                     \
-      reinterpret_cast<EO*>(out), q, n_heads, n_kv_heads, dh, d_kv, scale)
-#define MONE_ATTN(EA, EK, EO)                                                                   \
-  do {                                                                                          \
-    if (dh <= 128) MONE_ATTN_W(EA, EK, EO, 128);                                                \
-    else MONE_ATTN_W(EA, EK, EO, 256);                                                          \
-  } while (0)
-  if (act_bf16) {
-    if (kbf) { if (obf) MONE_ATTN(bf16_t, bf16_t, bf16_t); else MONE_ATTN(bf16_t, bf16_t, float); }
-    else { if (obf) MONE_ATTN(bf16_t, float, bf16_t); else MONE_ATTN(bf16_t, float, float); }
-  } else {
-    if (kbf) { if (obf) MONE_ATTN(float, bf16_t, bf16_t); else MONE_ATTN(float, bf16_t, float); }
-    else { if (obf) MONE_ATTN(float, float, bf16_t); else MONE_ATTN(float, float, float); }
-  }
-#undef MONE_ATTN
-#undef MONE_ATTN_W
-  hipError_t e = hipGetLastError();
+  Attention p{};
+  p.qh = qh; p.kh = kh; p.vh = vh; p.kv_mem = kv_mem; p.out = out;
+  p.L = L; p.q = q; p.n_heads = n_heads; p.n_kv_heads = n_kv_heads; p.dh = dh; p.d_kv = d_kv;
+  p.scale = 1.0f / std::sqrt((float)dh);
+  p.act_bf16 = act_bf16;
+  p.mem_bf16 = kv_dtype == MONE_BF16;
+  p.out_bf16 = out_dtype == MONE_BF16;
+  const hipError_t e = launch_attention_kernel(p, s);
   if (e != hipSuccess) return hip_fail(e, "launch ATTN");
   return MONE_OK;
 }

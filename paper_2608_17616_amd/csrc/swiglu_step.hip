@@ -51,14 +51,6 @@ __device__ __forceinline__ float const_load(const float* p) {
   return *(const __attribute__((address_space(4))) float*)p;
 }
 
-// This wave's LDS accesses are done; global loads stay in flight over the barrier.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_s_waitcnt((63 & 15) | ((63 >> 4) << 14) | (7 << 4));  // lgkmcnt(0)
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 template <int NB, bool PAPER>
 struct StepLds {
   static constexpr int NK = 2 * NB;           // contraction steps over the channels (16 each)

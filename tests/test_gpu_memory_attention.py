@@ -117,3 +117,74 @@ def test_memory_attention_rejects_bad_arguments(torch_cuda):
                                     None) == mone.MONE_EUNSUPPORTED
     sw.close()
     sess.close()
+
+
+# ---------------------------------------------------------------- the kernel's edges
+# Head widths around the padded ones (32, 64, 128, 256), also odd (element by element loads), row
+# blocks of 32 and their remainders, groups of 1 to 7 query heads over the 4 waves, every dtype
+# combination.  Bars: a score of up to about 8 carries a relative error of some 10 roundings of
+# 2^-24, so the probabilities, and with them an fp32 output, one of 5e-6; a bf16 output adds its
+# own rounding, 2^-9 at most.
+
+def _attention_case(torch, L, d_kv, q, hq, hkv, act, kvd, outd, edit=None):
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16}
+    code = {"f32": mone.MONE_F32, "bf16": mone.MONE_BF16}
+    dh = d_kv // hkv
+    cfg = C("attn_edge", n_layers=L, d_model=64, d_hidden=64, d_kv=d_kv, seg_len=64,
+            n_context=64, act_dtype=act, lr=0.0)
+    prob = DeviceProblem(cfg, [])
+    sess = mone.TtlSession(cfg, prob.wkv, prob.w1, prob.w2)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(q * 1000 + d_kv)
+    r = lambda t, *s: torch.randn(*s, generator=gen, device="cuda").to(dt[t])  # noqa: E731
+    qh, kh, vh = r(act, L, q, hq * dh), r(act, L, q, hkv * dh), r(act, L, q, hkv * dh)
+    kv = r(kvd, L, q, 2 * d_kv)
+    if edit:
+        edit(qh, kh, vh, kv)
+    # rows past q in the caller's buffer stay as they are
+    out = torch.full((L * q + 1, hq * dh), 7.0, dtype=dt[outd], device="cuda")
+    print(f"[attn] L={L} d_kv={d_kv} q={q} {hq}/{hkv} {act} {kvd} {outd}", flush=True)
+    mone.mone_memory_attention(sess.handle, qh, kh, vh, kv, code[kvd], q, hq, hkv, out,
+                               code[outd])
+    torch.cuda.synchronize()
+    sess.close()
+    assert bool((out[-1] == 7.0).all())
+    host = [t.double().cpu().numpy() for t in (qh, kh, vh, kv)]
+    return out[:-1].view(L, q, -1).double().cpu().numpy(), host
+
+
+@pytest.mark.parametrize("d_kv,q,hq,hkv", [
+    (64, 33, 64, 64), (64, 1, 3, 1), (320, 65, 16, 16), (320, 100, 24, 8), (192, 31, 2, 2),
+    (128, 97, 14, 2), (256, 64, 8, 2), (192, 40, 1, 1), (256, 161, 5, 1), (256, 5, 16, 8)])
+@pytest.mark.parametrize("act,kvd,outd", [("bf16", "bf16", "bf16"), ("bf16", "f32", "f32"),
+                                          ("f32", "bf16", "f32"), ("f32", "f32", "f32")])
+def test_attention_kernel_edges(torch_cuda, d_kv, q, hq, hkv, act, kvd, outd):
+    L = 2
+    got, (qn, kn, vn, mn) = _attention_case(torch_cuda, L, d_kv, q, hq, hkv, act, kvd, outd)
+    for l in range(L):
+        e = rel_l2(got[l], orc.memory_attention(qn[l], kn[l], vn[l], mn[l], hq, hkv))
+        assert e <= (5e-6 if outd == "f32" else 4e-3), (l, e)
+
+
+@pytest.mark.parametrize("act,kvd", [("bf16", "f32"), ("f32", "f32"), ("f32", "bf16")])
+def test_attention_kernel_infinities(torch_cuda, act, kvd):
+    """An infinite value reaches every row that sees it and its own column only; a key of minus
+    infinity along a positive query channel has probability zero."""
+    q, d_kv, inf = 70, 64, float("inf")
+
+    def edit(qh, kh, vh, kv):
+        vh[0, 40, 3] = inf          # query-side value of position 40
+        kv[0, 50, d_kv + 9] = -inf  # memory value of position 50
+        qh[0, :, 5] = 1.5
+        kh[0, 7, 5] = -inf          # position 7's own key is never chosen
+    got, (qn, kn, vn, mn) = _attention_case(torch_cuda, 1, d_kv, q, 1, 1, act, kvd, "f32", edit)
+    with np.errstate(invalid="ignore"):
+        for i in range(q):
+            s = np.concatenate([kn[0, :i + 1] @ qn[0, i], mn[0, :i + 1, :d_kv] @ qn[0, i]])
+            p = np.exp((s - s.max()) / np.sqrt(d_kv))
+            p /= p.sum()
+            v = np.concatenate([vn[0, :i + 1], mn[0, :i + 1, d_kv:]])
+            want = np.where(p[:, None] > 0, p[:, None] * v, 0.0).sum(0)
+            fin = np.isfinite(want)
+            assert np.array_equal(got[0, i][~fin], want[~fin]), i
+            assert rel_l2(got[0, i][fin], want[fin]) <= 2e-5, i
