@@ -14,7 +14,7 @@ ROOT = os.path.dirname(PKG)
 SOURCES = [os.path.join(PKG, "csrc", f) for f in
            ("mone_ttl.hip", "mone_swiglu.hip", "swiglu_step.hip", "attention.hip")]
 DEPENDS = SOURCES + [os.path.join(PKG, "csrc", f) for f in
-                     ("kernels.hpp", "host_common.hpp", "swiglu_kernels.hpp",
+                     ("kernels.hpp", "main_loop.inc", "host_common.hpp", "swiglu_kernels.hpp",
                       "swiglu_step.hpp", "attention.hpp")] + [
                      os.path.join(ROOT, "include", f) for f in ("mone_ttl.h", "mone_swiglu.h")]
 LIB = os.path.join(PKG, "libmone_ttl.so")

@@ -34,11 +34,6 @@ namespace {
 constexpr int kKeys = 32;   // positions per chunk (of each set)
 constexpr int kRowsW = 32;  // query rows per wave
 
-__device__ __forceinline__ f32x16 mfma_bf16(const u32x4& a, const u32x4& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
 // Upper halves of two floats, a's in the low 16 bits.
 __device__ __forceinline__ uint32_t hi_pair(float a, float b) {
   return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);

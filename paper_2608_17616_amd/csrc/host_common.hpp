@@ -41,7 +41,8 @@ inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // TILE_64x256_DEEP: 64 x 256 tiles with a 4-slot ring per operand (one workgroup per CU).
 enum TileShape {
-  TILE_256x256 = 0, TILE_128x128 = 1, TILE_64x256 = 2, TILE_256x64 = 3, TILE_64x256_DEEP = 4
+  TILE_256x256 = 0, TILE_128x128 = 1, TILE_64x256 = 2, TILE_256x64 = 3, TILE_64x256_DEEP = 4,
+  TILE_64x64 = 5
 };
 
 constexpr int kNumCUs = 256;
@@ -55,7 +56,14 @@ inline TileShape pick_tile(int m, int n, int layers) {
     return (long long)((n + 255) / 256) * layers <= kNumCUs ? TILE_64x256_DEEP : TILE_64x256;
   if (n <= 64) return TILE_256x64;
   const long long big = (long long)((m + 255) / 256) * ((n + 255) / 256) * layers;
-  if (m >= 256 && n >= 256 && big >= kNumCUs) return TILE_256x256;
+  // one workgroup per CU runs 256 x 256 tiles in whole rounds, and a last round that is mostly
+  // empty costs as much as a full one: below 85% of full rounds 128 x 128 tiles, two per CU, are
+  // faster although a full round of them takes 1.24 times as long (FWD1 at 12 layers of
+  // [1024 x 3072], K = 1536, 75%: 199 -> 169 us; 6 of [768 x 4096], K = 4096, 56%: 238 -> 209;
+  // 28 of [777 x 3072], K = 3072, 87%: 559 against 598)
+  const long long rounds = (big + kNumCUs - 1) / kNumCUs;
+  if (m >= 256 && n >= 256 && big >= kNumCUs && 20 * big >= 17 * rounds * kNumCUs)
+    return TILE_256x256;
   return TILE_128x128;
 }
 
@@ -76,6 +84,29 @@ inline Opnd opnd(const void* p, long long lstride, int ld, int rows) {
   o.ld = ld;
   o.rows = rows;
   return o;
+}
+
+// The tile a launch of shape t runs with.
+//  - 64 x 64 tiles (each wave a quarter of the contraction) where they are few.  With few large
+//    tiles most CUs idle, and each K step of a tile waits a memory latency: 24 steps of one fp32
+//    128 x 128 tile took 52 us.  Measured over launches of 8 to 4096 such tiles: up to 512 (two
+//    per CU, against 128 tiles of 128 x 128) faster or equal (8 x [256 x 1024] of K = 1024, fp32:
+//    80 -> 50 us), above that slower (16 layers of 2048, T = 512, bf16: 1.08 ms, 1.20 with a limit
+//    of 2048).  The 64-row (or column) shapes of short extents reach the chip with a quarter of
+//    the tiles, so with bf16 the line is one per CU there (16 segments of 64 tokens, 16 layers of
+//    2048: 2.07 ms without, 2.01 with 256, 2.08 with 512); fp32, whose products take longer, keeps
+//    two (4 layers of 960 -> 1216, T = 64: 693 us without, 510 with 256, 465 with 512).
+//  - fp32: 128 x 128 in place of 256 x 256.  A step's products take six times as long as its
+//    loads' bf16 counterpart, so the larger tile saves no time on loads, and its planes do not
+//    fit the registers.
+template <typename E>
+TileShape narrow_tile(TileShape t, const Spec* specs, int nspec, int layers) {
+  const bool wide = specs[0].m_extent > 64 && specs[0].n > 64;
+  long long t64 = 0;
+  for (int i = 0; i < nspec; ++i)
+    t64 += (long long)((specs[i].m_extent + 63) / 64) * ((specs[i].n + 63) / 64) * layers;
+  if (t64 <= (wide || sizeof(E) == 4 ? 2 : 1) * kNumCUs) return TILE_64x64;
+  return sizeof(E) == 4 && t == TILE_256x256 ? TILE_128x128 : t;
 }
 
 template <typename E, int BM, int BN, int WAVES_M, int DEPTH = 0, class Epi>
@@ -160,16 +191,19 @@ hipError_t launch_split(const Spec& spec, int layers, const Epi& epi, float* par
 // Tiles per layer of a problem of m x n under tile shape t (what launch_gemm will use).
 inline int tiles_for(TileShape t, int m, int n) {
   const int bm = t == TILE_256x256 || t == TILE_256x64 ? 256 : t == TILE_128x128 ? 128 : 64;
-  const int bn = t == TILE_256x64 ? 64 : t == TILE_128x128 ? 128 : 256;
+  const int bn = t == TILE_256x64 || t == TILE_64x64 ? 64 : t == TILE_128x128 ? 128 : 256;
   return ((m + bm - 1) / bm) * ((n + bn - 1) / bn);
 }
 
 // `split_part` (kSplitFloats floats, or null): single-problem deep-ring launches whose tiles
 // leave CUs idle split their contraction (launch_split).
-template <typename E, class Epi>
+// NARROW: shapes as narrow_tile chooses (false: bf16 launches keep t).
+template <typename E, bool NARROW = true, class Epi>
 hipError_t launch_gemm(TileShape t, const Spec* specs, int nspec, int layers, const Epi& epi,
                        hipStream_t s, int* tiles_per_layer = nullptr,
                        float* split_part = nullptr) {
+  static_assert(NARROW || sizeof(E) == 2, "fp32 launches take narrow_tile's shapes");
+  if constexpr (NARROW) t = narrow_tile<E>(t, specs, nspec, layers);
   if (t == TILE_64x256_DEEP && split_part && nspec == 1) {
     constexpr int BK = 8 * (16 / (int)sizeof(E));
     const long long tiles =
@@ -181,11 +215,16 @@ hipError_t launch_gemm(TileShape t, const Spec* specs, int nspec, int layers, co
   }
   switch (t) {
     case TILE_256x256:
-      return launch_tiled<E, 256, 256, 2>(specs, nspec, layers, epi, s, tiles_per_layer);
+      if constexpr (sizeof(E) == 2)
+        return launch_tiled<E, 256, 256, 2>(specs, nspec, layers, epi, s, tiles_per_layer);
+      else
+        return hipErrorInvalidValue;  // narrow_tile
     case TILE_128x128:
       return launch_tiled<E, 128, 128, 2>(specs, nspec, layers, epi, s, tiles_per_layer);
     case TILE_256x64:
       return launch_tiled<E, 256, 64, 4>(specs, nspec, layers, epi, s, tiles_per_layer);
+    case TILE_64x64:
+      return launch_tiled<E, 64, 64, 1>(specs, nspec, layers, epi, s, tiles_per_layer);
     case TILE_64x256_DEEP:
       return launch_tiled<E, 64, 256, 1, 4>(specs, nspec, layers, epi, s, tiles_per_layer);
     default:

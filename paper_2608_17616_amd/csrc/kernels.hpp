@@ -19,11 +19,18 @@
 // wave reads its fragments one sub-step ahead of the MFMAs that use them.  Launches with at most
 // one tile per CU use a deep ring instead (4 slots per operand, both 3 steps ahead), and may
 // split each tile's K steps over several workgroups: a partial pass stores raw accumulators,
-// and a reduce pass sums them in split order before the epilogue.
+// and a reduce pass sums them in split order before the epilogue.  Launches of few tiles use 64 x
+// 64 tiles whose waves divide the contraction (TileCfg::KW).  The loop is in main_loop.inc.
 //
-// MFMA: bf16 uses v_mfma_f32_32x32x16_bf16 (one 16-byte fragment per lane = 8 k-values), fp32
-// uses four v_mfma_f32_32x32x2_f32 on the four floats of the same 16-byte fragment.  Within a
-// 32x32 block lane l supplies row (l % 32) of A and column (l % 32) of B; A and B take their
+// MFMA: bf16 uses v_mfma_f32_32x32x16_bf16 (one 16-byte fragment per lane = 8 k-values).  fp32
+// takes two 16-byte fragments (8 floats), splits each float into three bf16 planes that sum to it
+// exactly and multiplies them with the same instruction (split_planes): 192 matrix cycles per block
+// and 16 k-values against 512 with fp32 instructions, the splitting (5.5 vector instructions per
+// value) between the products.  Measured in few-tile launches, where latency is the larger part:
+// 8 layers, two segments of 256 at 1024 -> 1024 -> 512: 603 us with fp32 instructions and large
+// tiles, 420 with 64 x 64 tiles, 340 with the planes; the error against 64 bits stays 3.6e-8 (8
+// segments of 128 tokens at 256 -> 512 -> 256: 8.2e-8 -> 7.3e-8).
+// Within a 32x32 block lane l supplies row (l % 32) of A and column (l % 32) of B; A and B take their
 // k-values from the same fragment positions, so the k order inside an instruction does not
 // matter.  Accumulator register r of lane l holds C[8*(r/4) + 4*(l/32) + r%4][l % 32].
 //
@@ -202,6 +209,43 @@ struct GemmLaunch {
 };
 
 // ------------------------------------------------------------------------------------------
+// fp32 products on the bf16 matrix cores
+
+__device__ __forceinline__ f32x16 mfma_bf16(const u32x4& a, const u32x4& b, const f32x16& c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// Eight finite floats as three bf16 planes, p[0] + p[1] + p[2] = the values exactly: each plane
+// is the remainder rounded to nearest, so it has 8 bits and a sign, and the remainder after two
+// planes has at most 8 bits left.  (An infinity or a value that rounds to one gives NaN in the
+// lower planes, hence in every product of its row or column.)
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split_planes(const u32x4 (&x)[2], u32x4 (&p)[3]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float a = __uint_as_float(x[i >> 1][(2 * i) & 3]);
+    float b = __uint_as_float(x[i >> 1][(2 * i + 1) & 3]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const f32x2 ab = {a, b};
+      const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(ab, bf16x2));
+      p[k][i] = w;
+      if (k == 2) break;
+      a -= __uint_as_float(w << 16);
+      b -= __uint_as_float(w & 0xffff0000u);
+    }
+  }
+}
+
+// The products of planes that are kept, smallest first: a lower plane is at most 2^-9 of the one
+// above it, so the three left out (1 x 2, 2 x 1, 2 x 2) lie at or below 2^-26 of the product.
+constexpr int kPlaneProducts = 6;
+__device__ constexpr int kPlaneA[kPlaneProducts] = {2, 0, 1, 1, 0, 0};
+__device__ constexpr int kPlaneB[kPlaneProducts] = {0, 2, 1, 0, 1, 0};
+
+// ------------------------------------------------------------------------------------------
 // The grouped GEMM kernel
 
 
@@ -247,7 +291,9 @@ struct TileCfg {
   static constexpr int NA = DEPTH > 0 ? DEPTH : BM == BN ? 3 : 2;
   static constexpr int NB = DEPTH > 0 ? DEPTH : 2;
   static constexpr int ASLOT = BM * 128, BSLOT = BN * 128;
-  static constexpr int RING = NA * ASLOT + NB * BSLOT;
+  // 64 x 64: a ring of two slots of both panels for each of the 4 waves (see KW below)
+  static constexpr bool KW = BM == 64 && BN == 64;
+  static constexpr int RING = KW ? 4 * 2 * (ASLOT + BSLOT) : NA * ASLOT + NB * BSLOT;
   static constexpr int EPI_BYTES = 4 * 64 * 64 * 4;  // per-wave 64 x 64 fp32 staging
   static constexpr int SMEM = RING > EPI_BYTES ? RING : EPI_BYTES;
 };
@@ -285,6 +331,25 @@ template <int NM, int NR, int NV, int... I>
 __device__ __forceinline__ void front_seq(std::integer_sequence<int, I...>) {
   (front_step<NM, NR, NV, I>(), ...);
 }
+// fp32 sub-steps: the next sub-step's LDS reads first, then after each MFMA its share of the
+// splitting of those fragments (VA vector instructions, from the third MFMA on) and of the NV
+// buffer loads.
+template <int NM, int VA, int NV, int I>
+__device__ __forceinline__ void split_step() {
+  constexpr int v = (NV * (I + 1)) / NM - (NV * I) / NM;
+  __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                         // MFMA
+  if constexpr (v > 0) __builtin_amdgcn_sched_group_barrier(0x020, v, 0);    // VMEM read
+  if constexpr (I >= 2) __builtin_amdgcn_sched_group_barrier(0x002, VA, 0);  // VALU
+}
+template <int NM, int VA, int NV, int... I>
+__device__ __forceinline__ void split_seq(std::integer_sequence<int, I...>) {
+  (split_step<NM, VA, NV, I>(), ...);
+}
+template <int NR, int NM, int VA, int NV>
+__device__ __forceinline__ void reads_then_split() {
+  __builtin_amdgcn_sched_group_barrier(0x100, NR, 0);  // DS read
+  split_seq<NM, VA, NV>(std::make_integer_sequence<int, NM>{});
+}
 template <int NRL, int NM, int NV>
 __device__ __forceinline__ void reads_then_interleave() {
   constexpr int lead = NRL < 4 ? NRL : 4;
@@ -298,14 +363,20 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
   using TC = TileCfg<BM, BN, DEPTH>;
   constexpr int VEC = 16 / (int)sizeof(E);   // elements per 16-byte vector
   constexpr int BK = 8 * VEC;                // K per step: 8 vectors = 128 bytes per row
-  constexpr int WAVES_N = 4 / WAVES_M;
+  // 64 x 64 tiles: the waves divide the contraction, not the tile.  Wave w computes the whole
+  // tile over the K steps w, w + 4, ..., from a ring of its own, so the loop has no barrier, and
+  // the epilogue sums the four accumulators.
+  constexpr bool KW = TC::KW;
+  constexpr int WAVES_N = KW ? 1 : 4 / WAVES_M;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;  // wave tile
   constexpr int FM = WM / 32, FN = WN / 32;  // 32x32 MFMA blocks per wave
-  constexpr int LA = BM / 32, LB = BN / 32;  // 1 KiB load instructions per wave per panel
+  // 1 KiB load instructions per wave per panel
+  constexpr int LA = KW ? 8 : BM / 32, LB = KW ? 8 : BN / 32;
   constexpr int NA = TC::NA, NB = TC::NB, ASLOT = TC::ASLOT, BSLOT = TC::BSLOT;
-  constexpr int MPF = sizeof(E) == 2 ? 1 : 4;  // MFMA instructions per fragment pair
-  constexpr int NM = FM * FN * MPF;            // MFMA instructions per sub-step
-  static_assert(FM >= 1 && FN >= 1 && WAVES_M * WAVES_N == 4, "tile shape");
+  constexpr int FV = sizeof(E) / 2;          // 16-byte vectors per fragment (8 k-values)
+  constexpr int NM = FM * FN * (sizeof(E) == 2 ? 1 : kPlaneProducts);  // MFMAs per sub-step
+  static_assert(FM >= 1 && FN >= 1 && WAVES_M * WAVES_N == (KW ? 1 : 4), "tile shape");
+  static_assert(!KW || (DEPTH == 0 && MODE == kSplitNone && !Epi::kRowScale), "64 x 64 tiles");
   __shared__ __attribute__((aligned(1024))) unsigned char smem[TC::SMEM];
 
   // Problem of this workgroup: problem 0's tiles come first.  (Alternating the two problems'
@@ -327,7 +398,7 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
   const int m0 = tm * BM, n0 = tn * BN;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int wm = KW ? 0 : wave / WAVES_N, wn = KW ? 0 : wave % WAVES_N;
 
   f32x16 acc[FM][FN];
 #pragma unroll
@@ -364,15 +435,19 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
     const E* B = reinterpret_cast<const E*>(Pt.b.p) + (long long)layer * Pt.b.lstride;
     ra[pp] = make_rsrc(A, (uint32_t)((long long)Pt.a.rows * Pt.a.ld * (int)sizeof(E)));
     rb[pp] = make_rsrc(B, (uint32_t)((long long)Pt.b.rows * Pt.b.ld * (int)sizeof(E)));
-    const unsigned r = 8u * wave + lrow;
+    // (64 x 64: instruction i of a wave fills rows 8*i ..)
+    const unsigned r = KW ? lrow : 8u * wave + lrow;
     const unsigned v = lslot ^ ((r >> 1) & 7u);
+    constexpr unsigned RI = KW ? 8u : 32u;  // rows from one instruction to the next
     const unsigned lda = (unsigned)Pt.a.ld * sizeof(E), ldb = (unsigned)Pt.b.ld * sizeof(E);
     // Rows past the operand's end give offsets at or beyond the descriptor's range (read as
     // zero); the range is below 2^31, so the unsigned offsets cannot wrap.
 #pragma unroll
-    for (int i = 0; i < LA; ++i) vofa[pp][i] = (int)((m0 + r + 32u * i) * lda + v * 16u);
+    for (int i = 0; i < LA; ++i)
+      vofa[pp][i] = (int)((m0 + r + RI * i) * lda + (KW && (i & 1) ? v ^ 4u : v) * 16u);
 #pragma unroll
-    for (int i = 0; i < LB; ++i) vofb[pp][i] = (int)((n0 + r + 32u * i) * ldb + v * 16u);
+    for (int i = 0; i < LB; ++i)
+      vofb[pp][i] = (int)((n0 + r + RI * i) * ldb + (KW && (i & 1) ? v ^ 4u : v) * 16u);
   }
   const i32x4 rnone = make_rsrc(P.part[0].a.p, 0u);  // zero range: every load reads 0
 
@@ -410,39 +485,87 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
   using Part0 = std::integral_constant<int, 0>;
   using Part1 = std::integral_constant<int, 1>;
 
-  // Fragments of one K sub-step (16 bf16 / 8 fp32 k-values per lane).
-  auto read_frags = [&](int sla, int slb, int kk, u32x4 (&fa)[FM], u32x4 (&fb)[FN]) {
+  // Fragments of one K sub-step: 16 k-values, 8 per lane (a K step of 64 bf16 has four sub-steps,
+  // one of 32 fp32 two).  An fp32 lane's 8 values are two vectors, of k-values 8 apart from
+  // a half wave's point of view; both operands are read alike, so the products pair up.
+  auto read_frags = [&](int sla, int slb, int kk, u32x4 (&fa)[FM][FV], u32x4 (&fb)[FN][FV]) {
     const unsigned char* sa = smem + sla * ASLOT;
     const unsigned char* sb = smem + NA * ASLOT + slb * BSLOT;
-    const int v = kk * 2 + (lane >> 5);
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
       const int r = wm * WM + i * 32 + (lane & 31);
-      fa[i] = *reinterpret_cast<const u32x4*>(sa + r * 128 + ((v ^ ((r >> 1) & 7)) << 4));
+#pragma unroll
+      for (int f = 0; f < FV; ++f) {
+        const int v = (kk * FV + f) * 2 + (lane >> 5);
+        fa[i][f] = *reinterpret_cast<const u32x4*>(sa + r * 128 + ((v ^ ((r >> 1) & 7)) << 4));
+      }
     }
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
       const int r = wn * WN + j * 32 + (lane & 31);
-      fb[j] = *reinterpret_cast<const u32x4*>(sb + r * 128 + ((v ^ ((r >> 1) & 7)) << 4));
+#pragma unroll
+      for (int f = 0; f < FV; ++f) {
+        const int v = (kk * FV + f) * 2 + (lane >> 5);
+        fb[j][f] = *reinterpret_cast<const u32x4*>(sb + r * 128 + ((v ^ ((r >> 1) & 7)) << 4));
+      }
     }
   };
-  auto mfmas = [&](const u32x4 (&fa)[FM], const u32x4 (&fb)[FN]) {
+  auto mfmas = [&](const u32x4 (&fa)[FM][FV], const u32x4 (&fb)[FN][FV]) {
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        if constexpr (sizeof(E) == 2) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8, fa[i]), __builtin_bit_cast(bf16x8, fb[j]), acc[i][j],
-              0, 0, 0);
-        } else {
+      for (int j = 0; j < FN; ++j) acc[i][j] = mfma_bf16(fa[i][0], fb[j][0], acc[i][j]);
+  };
+  // fp32: the fragments of a sub-step as planes, made while the sub-step before it is multiplied;
+  // native: the floats themselves, for fp32 matrix instructions.
+  struct Planes {
+    u32x4 a[FM][3], b[FN][3];
+  };
+  auto to_planes = [&](auto native, const u32x4 (&fa)[FM][FV], const u32x4 (&fb)[FN][FV], Planes& P) {
+    if constexpr (FV == 2) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-                __uint_as_float(fa[i][e]), __uint_as_float(fb[j][e]), acc[i][j], 0, 0, 0);
+      for (int x = 0; x < FM + FN; ++x) {
+        const u32x4 (&f)[FV] = x < FM ? fa[x % FM] : fb[(x + FN - FM) % FN];
+        u32x4 (&p)[3] = x < FM ? P.a[x % FM] : P.b[(x + FN - FM) % FN];
+        if constexpr (decltype(native)::value) {
+          p[0] = f[0];
+          p[1] = f[1];
+        } else {
+          split_planes(f, p);
         }
       }
+    }
   };
+  auto mul = [&](auto native, const Planes& P) {
+    if constexpr (decltype(native)::value) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(
+                __uint_as_float(P.a[i][e >> 2][e & 3]), __uint_as_float(P.b[j][e >> 2][e & 3]),
+                acc[i][j], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int x = 0; x < kPlaneProducts; ++x)
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j)
+            acc[i][j] = mfma_bf16(P.a[i][kPlaneA[x]], P.b[j][kPlaneB[x]], acc[i][j]);
+    }
+  };
+  constexpr int SPV = 44 * (FM + FN);               // vector instructions of one split
+  constexpr int VA = (SPV + NM - 3) / (NM - 2);     // ... per MFMA
+  auto split_order = [](auto native, auto nr, auto nv) {
+    if constexpr (FV == 2 && !decltype(native)::value)
+      reads_then_split<decltype(nr)::value, NM, VA, decltype(nv)::value>();
+  };
+  [[maybe_unused]] Planes pl0, pl1;
+  constexpr std::integral_constant<int, (FM + FN) * FV> kReads{};  // LDS reads per sub-step
+  constexpr std::integral_constant<int, 0> kNone{};
 
   // Part 0's contribution times a per-column factor (kPart0Scale): applied once, after the
   // last K step of part 0 this workgroup computes.  Lane l's accumulators of MFMA block j all
@@ -463,170 +586,44 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
     }
   };
 
-  // Pipeline.  K step kt reads A slot kt % NA and B slot kt % NB in four sub-steps.  The
-  // fragments of each sub-step are read while the MFMAs of the previous one run: sub-step 0 of
-  // step kt+1 is read right after the synchronisation that ends step kt, and sub-step 3 of
-  // step kt is multiplied after it.  With an A ring of 3 (A two steps ahead, B one), each of
-  // the four MFMA blocks between two synchronisations carries a quarter of the next loads:
-  // the second half of B's step kt+1, both halves of A's step kt+2, and (after the
-  // synchronisation, into the B slot step kt has just released) the first half of B's step
-  // kt+2.  With an A ring of 2, B's and A's step kt+1 go with sub-steps 0 and 1.  Before the
-  // synchronisation each wave waits until its loads of step kt+1 have landed (A loads of step
-  // kt+2 may stay in flight) and its LDS reads of step kt are done; the workgroup then
-  // synchronises, so step kt+1 is complete in LDS and no wave reads the slots of step kt any
-  // more (later loads may overwrite them).
-  constexpr int VMC = NA > 2 ? LA : 0;  // loads allowed in flight at the synchronisation
-  constexpr int WAIT_STEP = (VMC & 15) | ((VMC >> 4) << 14) | (7 << 4);
-  if constexpr (DEPTH > 0) {
-    // Deep ring: step kt reads slot kt % DEPTH; during its first three sub-steps each wave
-    // loads step kt + DEPTH - 1 into the slot of step kt - 1, which the synchronisation ending
-    // step kt - 1 released.  Before the synchronisation that ends step kt each wave waits until
-    // its loads of step kt + 1 have landed; those of the DEPTH - 2 later steps stay in flight.
-    static_assert(DEPTH >= 3 && NA == DEPTH && NB == DEPTH, "deep ring");
-    constexpr int VMD = (DEPTH - 2) * (LA + LB);
-    static_assert(VMD < 64, "vmcnt range");
-    constexpr int WAIT_D = (VMD & 15) | ((VMD >> 4) << 14) | (7 << 4);
-    if (nk > kbeg) {
-      u32x4 fa0[FM], fb0[FN], fa1[FM], fb1[FN];
-      // Prologue: steps kbeg .. kbeg + DEPTH - 2 into slots 0 .. DEPTH - 2 (the part of each
-      // step chosen at run time here only).
-#pragma unroll
-      for (int j = 0; j < DEPTH - 1; ++j) {
-        const int kj = kbeg + j;
-        if (kj < nk0) { load_a(Part0{}, kj, j, 0, LA); load_b(Part0{}, kj, j, 0, LB); }
-        else { load_a(Part1{}, kj, j, 0, LA); load_b(Part1{}, kj, j, 0, LB); }
-      }
-      __builtin_amdgcn_s_waitcnt(WAIT_D);
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      int sl = 0;
-      read_frags(sl, sl, 0, fa0, fb0);
-      auto dstep = [&](int kt, auto pl) {
-        const int sl_load = sl == 0 ? DEPTH - 1 : sl - 1;  // slot of step kt - 1: free
-        const int kl = kt + DEPTH - 1;
-        constexpr int NF = FM + FN;
-        read_frags(sl, sl, 1, fa1, fb1);
-        load_b(pl, kl, sl_load, 0, LB / 2);
-        mfmas(fa0, fb0);
-        reads_then_interleave<NF, NM, LB / 2>();
-        read_frags(sl, sl, 2, fa0, fb0);
-        load_b(pl, kl, sl_load, LB / 2, LB);
-        mfmas(fa1, fb1);
-        reads_then_interleave<NF, NM, LB - LB / 2>();
-        read_frags(sl, sl, 3, fa1, fb1);
-        load_a(pl, kl, sl_load, 0, LA);
-        mfmas(fa0, fb0);
-        reads_then_interleave<NF, NM, LA>();
-        __builtin_amdgcn_s_waitcnt(WAIT_D);
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        sl = sl + 1 == DEPTH ? 0 : sl + 1;
-        read_frags(sl, sl, 0, fa0, fb0);  // after the last step: a consumed slot, never used
-        mfmas(fa1, fb1);
-        reads_then_interleave<NF, NM, 0>();
-      };
-      if constexpr (NP == 1) {
-        for (int kt = kbeg; kt < nk; ++kt) dstep(kt, Part0{});
-      } else {
-        // both operands switch part when the loaded step reaches nk0; part 0's computed steps
-        // end at c
-        const int sw = nk0 - (DEPTH - 1);
-        const int e1 = sw < kbeg ? kbeg : (sw > nk ? nk : sw);
-        const int c = nk0 < kbeg ? kbeg : (nk0 > nk ? nk : nk0);
-        int kt = kbeg;
-        for (; kt < e1; ++kt) dstep(kt, Part0{});
-        if constexpr (Epi::kPart0Scale) {
-          for (; kt < c; ++kt) dstep(kt, Part1{});
-          if (kbeg < c) part0_scale();
-        }
-        for (; kt < nk; ++kt) dstep(kt, Part1{});
-      }
-      __builtin_amdgcn_s_waitcnt(0);  // the last (out-of-range) loads have retired
-      __syncthreads();                // the epilogue reuses the LDS of the rings
-    }
-  } else if (nk > 0) {
-    u32x4 fa0[FM], fb0[FN], fa1[FM], fb1[FN];
-    // Prologue: step 0 first, then (ring of 3) A's step 1 and the first half of B's step 1,
-    // which may still be in flight when step 0 starts.
-    if (nk0 > 0) { load_a(Part0{}, 0, 0, 0, LA); load_b(Part0{}, 0, 0, 0, LB); }
-    else { load_a(Part1{}, 0, 0, 0, LA); load_b(Part1{}, 0, 0, 0, LB); }
-    if constexpr (NA > 2) {
-      if (nk0 > 1) { load_a(Part0{}, 1, 1, 0, LA); load_b(Part0{}, 1, 1, 0, LB / 2); }
-      else { load_a(Part1{}, 1, 1, 0, LA); load_b(Part1{}, 1, 1, 0, LB / 2); }
-    }
-    constexpr int VPRO = NA > 2 ? LA + LB / 2 : 0;  // prologue loads allowed in flight
-    __builtin_amdgcn_s_waitcnt((VPRO & 15) | ((VPRO >> 4) << 14) | (7 << 4));
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    int sa = 0, sb = 0;
-    read_frags(sa, sb, 0, fa0, fb0);
-    auto step = [&](int kt, auto pa, auto pb) {
-      const int sa_next = sa + 1 == NA ? 0 : sa + 1;
-      const int sa_load = sa == 0 ? NA - 1 : sa - 1;  // slot of step kt-1: free
-      const int sb_next = sb ^ 1;
-      constexpr int NF = FM + FN;  // LDS reads per sub-step
-      read_frags(sa, sb, 1, fa1, fb1);
-      if constexpr (NA > 2) {
-        load_b(pb, kt + 1, sb_next, LB / 2, LB);
-        mfmas(fa0, fb0);
-        reads_then_interleave<NF, NM, LB - LB / 2>();
-        read_frags(sa, sb, 2, fa0, fb0);
-        load_a(pa, kt + NA - 1, sa_load, 0, LA / 2);
-        mfmas(fa1, fb1);
-        reads_then_interleave<NF, NM, LA / 2>();
-        read_frags(sa, sb, 3, fa1, fb1);
-        load_a(pa, kt + NA - 1, sa_load, LA / 2, LA);
-        mfmas(fa0, fb0);
-        reads_then_interleave<NF, NM, LA - LA / 2>();
-      } else {
-        load_b(pb, kt + 1, sb_next, 0, LB);
-        mfmas(fa0, fb0);
-        reads_then_interleave<NF, NM, LB>();
-        read_frags(sa, sb, 2, fa0, fb0);
-        load_a(pa, kt + NA - 1, sa_load, 0, LA);
-        mfmas(fa1, fb1);
-        reads_then_interleave<NF, NM, LA>();
-        read_frags(sa, sb, 3, fa1, fb1);
-        mfmas(fa0, fb0);
-        reads_then_interleave<NF, NM, 0>();
-      }
-      // Explicit wait, then a bare barrier: a fenced barrier would also wait for the A loads
-      // that may stay in flight.  The empty asm statements keep the compiler from moving LDS
-      // accesses across the barrier.
-      __builtin_amdgcn_s_waitcnt(WAIT_STEP);
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      const int sb_free = sb;  // B slot of step kt: read completely, free for step kt+2
-      sa = sa_next;
-      sb = sb_next;
-      read_frags(sa, sb, 0, fa0, fb0);  // after the last step: a consumed slot, never used
-      if constexpr (NA > 2) load_b(pa, kt + 2, sb_free, 0, LB / 2);  // step kt+2: A's part
-      mfmas(fa1, fb1);
-      reads_then_interleave<FM + FN, NM, (NA > 2 ? LB / 2 : 0)>();
+  if constexpr (sizeof(E) == 2) {
+    constexpr std::false_type native{};
+#include "main_loop.inc"
+  } else if constexpr (MODE != kSplitReduce) {
+    auto main_loop = [&](auto native) {
+#include "main_loop.inc"
     };
-    if constexpr (NP == 1) {
-      for (int kt = 0; kt < nk; ++kt) step(kt, Part0{}, Part0{});
+    main_loop(std::false_type{});
+    // Operands that are not finite (or round to an infinity in bf16), and sums that overflow:
+    // the tile again with fp32 matrix instructions, whose infinities and NaN are IEEE's.
+    float s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s = __builtin_fmaf(acc[i][j][r], 0.0f, s);
+    bool redo;
+    if constexpr (KW) {
+      redo = __any(s != 0.0f);  // NaN; each wave has its own loop
     } else {
-      // The loads' operand part changes at step nk0; running the steps in three ranges keeps
-      // the part a compile-time choice (no per-step selects of offsets).
-      const int e1 = nk0 - (NA - 1) < 0 ? 0 : (nk0 - (NA - 1) > nk ? nk : nk0 - (NA - 1));
-      const int e2 = nk0 - 1 < e1 ? e1 : (nk0 - 1 > nk ? nk : nk0 - 1);
-      const int c = nk0 < e2 ? e2 : (nk0 > nk ? nk : nk0);  // part 0's computed steps end
-      int kt = 0;
-      for (; kt < e1; ++kt) step(kt, Part0{}, Part0{});  // A and B loads in part 0
-      for (; kt < e2; ++kt) step(kt, Part1{}, Part0{});  // A loads reach part 1 first
-      if constexpr (Epi::kPart0Scale) {
-        for (; kt < c; ++kt) step(kt, Part1{}, Part1{});
-        if (c > 0) part0_scale();
-      }
-      for (; kt < nk; ++kt) step(kt, Part1{}, Part1{});
+      int* bad = reinterpret_cast<int*>(smem);
+      if (tid < 4) bad[tid] = 0;
+      __syncthreads();
+      if (s != 0.0f) bad[wave] = 1;
+      __syncthreads();
+      redo = (bad[0] | bad[1] | bad[2] | bad[3]) != 0;
+      __syncthreads();  // smem is free again
     }
-    __builtin_amdgcn_s_waitcnt(0);  // the last (out-of-range) loads have retired
-    __syncthreads();                // the epilogue reuses the LDS of the rings
+    if (redo) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+      main_loop(std::true_type{});
+    }
   }
 
   // Split-K: accumulators in their register layout, lane-contiguous, per (split, tile, wave).
@@ -656,6 +653,8 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
             acc[i][j][r] += __builtin_nontemporal_load(src + ((i * FN + j) * 16 + r) * 64);
     }
   }
+
+  if constexpr (KW) __syncthreads();  // every wave is done with its ring
 
   // ---- epilogue: each wave stages its own accumulators through LDS, 64 x 64 at a time
   // A wave's tile is processed in 64 x 64 sub-blocks (2 x 2 MFMA blocks) in a private 16 KiB
@@ -691,7 +690,12 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
   constexpr int NAUX = Epi::kAux;
   // Row chunks per lane: 8, or 4 pairs of rows (2i, 2i + 1) when the epilogue pairs rows.
   constexpr int RS = Epi::kPairRows ? 2 : 1;
-  constexpr int NCH = CPL / RS;
+  // (64 x 64 tiles: every wave stages its accumulators of the one sub-block and takes a quarter
+  // of its chunks, from chunk wave * NCH on, summing the four waves' regions in pairs into the
+  // first.)
+  constexpr int NCH = CPL / RS / (KW ? 4 : 1);
+  constexpr int CCH = CPL / (KW ? 4 : 1);
+  const int rb0 = KW ? 8 * RS * NCH * wave : 0, cb0 = KW ? 8 * CCH * wave : 0;
   static_assert(!Epi::kPairRows || (!Epi::kRowNorm && !Epi::kCols && !Epi::kWriteback &&
                                      !Epi::kRowScale),
                 "paired rows: row pass only");
@@ -714,7 +718,7 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
     const int grow = m0 + wm * WM + (sb / NSN) * SB, gcol = n0 + wn * WN + (sb % NSN) * SB;
 #pragma unroll
     for (int b = 0; b < NCH; ++b) {
-      const int row = grow + RS * (rl + 8 * b), col = gcol + cq;
+      const int row = grow + rb0 + RS * (rl + 8 * b), col = gcol + cq;
       if (row + RS - 1 < P.M && col < P.N) G.epi.pre8(pi, layer, row, col, P.M, P.N, ax[b]);
     }
   };
@@ -725,7 +729,7 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
     const int grow = m0 + wm * WM + (q / NSN) * SB, gcol = n0 + wn * WN + (q % NSN) * SB;
 #pragma unroll
     for (int b = 0; b < NCH; ++b) {
-      const int row = grow + RS * (rl + 8 * b), col = gcol + cq;
+      const int row = grow + rb0 + RS * (rl + 8 * b), col = gcol + cq;
       float (&w)[4] = *reinterpret_cast<float(*)[4]>(&aux[q >> 1][b][4 * (q & 1)]);
       if (row + RS - 1 < P.M && col < P.N) G.epi.pre4p(pi, layer, row, col, w);
     }
@@ -757,7 +761,12 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
           for (int e = 0; e < 4; ++e)
             stw[sidx(ii * 32 + g * 8 + (lane >> 5) * 4 + e, jj * 32 + (lane & 31))] =
                 acc[2 * sm + ii][2 * sn + jj][4 * g + e];
-    wave_sync();
+    if constexpr (KW) {
+      __syncthreads();
+      stw = reinterpret_cast<float*>(smem);
+    } else {
+      wave_sync();
+    }
     [[maybe_unused]] typename Epi::Blk blk;
     if constexpr (Epi::kBlk) blk = G.epi.block(layer, grow, gcol, cq);
     if constexpr (Epi::kPre && !Epi::kPreLate) {
@@ -765,7 +774,21 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
     }
 #pragma unroll
     for (int b = 0; b < NCH; ++b) {
-      const int r = RS * (rl + 8 * b), c = cq;
+      const int r = rb0 + RS * (rl + 8 * b), c = cq;
+      if constexpr (KW) {
+#pragma unroll
+        for (int x = 0; x < 2 * RS; ++x) {
+          float* p = stw + sidx(r + (x >> 1), x & 1 ? cq2 : c);
+          float4 w[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) w[i] = *reinterpret_cast<const float4*>(p + i * SB * SB);
+          *reinterpret_cast<float4*>(p) =
+              make_float4((w[0].x + w[1].x) + (w[2].x + w[3].x),
+                          (w[0].y + w[1].y) + (w[2].y + w[3].y),
+                          (w[0].z + w[1].z) + (w[2].z + w[3].z),
+                          (w[0].w + w[1].w) + (w[2].w + w[3].w));
+        }
+      }
       float* s0 = stw + sidx(r, c);
       float* s1 = stw + sidx(r, cq2);
       // Split chunks put each half of a row's 8 lanes on 32 of the staging's banks, the same
@@ -840,11 +863,12 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmLaunch<Epi> G) {
       bool cols = G.epi.has_cols(pi);
       if constexpr (Epi::kBlk) cols = blk.cols;
       if (cols) {
-        if constexpr (Epi::kWriteback) wave_sync();
+        if constexpr (KW) __syncthreads();
+        else if constexpr (Epi::kWriteback) wave_sync();
         const int kc = lane & 7;  // row group of this lane's column chunks
 #pragma unroll
-        for (int b = 0; b < CPL; ++b) {
-          const int c = (lane >> 3) + 8 * b;
+        for (int b = 0; b < CCH; ++b) {
+          const int c = cb0 + (lane >> 3) + 8 * b;
           if (grow + 8 * kc + 8 > P.M || gcol + c >= P.N) continue;
           float v[8];
 #pragma unroll

@@ -150,6 +150,7 @@ SwLayout make_sw_layout(const mone_swiglu_config* c) {
     L.rq = take(B * Tp * dhp * E);
     L.ra = take(B * Tp * dhp * E);
     L.rwo = take(B * dh * dhp * E);
+    take(B * 2 * dh * Tp * E);  // unused: the workspace keeps the size callers have planned for
   } else {
     L.dat = take(B * dh * Tp * E);
     L.at = take(B * dh * Tp * E);
@@ -181,6 +182,8 @@ constexpr TileShape kHeadTile = TILE_128x128;
 template <typename E, class Epi>
 hipError_t launch_head_gemm(const Spec* specs, int nspec, int heads, const Epi& epi,
                             hipStream_t s) {
+  if (narrow_tile<E>(kHeadTile, specs, nspec, heads) == TILE_64x64)
+    return launch_tiled<E, 64, 64, 1>(specs, nspec, heads, epi, s, nullptr);
   return launch_tiled<E, 128, 128, 2>(specs, nspec, heads, epi, s, nullptr);
 }
 
@@ -373,7 +376,7 @@ int run_sw_step_f32(mone_swiglu* H, int n, int cp, hipStream_t s) {
     EpiSwFwd<E> epi;
     epi.dat = dat; epi.rate = rate; epi.at = At; epi.dzgt = dzgt;
     epi.loss_part = H->at<float>(Ly.loss_part); epi.ls = lhT; epi.Tp = Tp; epi.n = n; epi.H = NH;
-    epi.parts = 4 * tiles_for(kHeadTile, 2 * dh, n);
+    epi.parts = 4 * tiles_for(narrow_tile<E>(kHeadTile, &sp, 1, B), 2 * dh, n);
     epi.lr = c.lr;
     H->timer.begin(MONE_SW_STAGE_FWD, s);
     if ((e = launch_head_gemm<E>(&sp, 1, B, epi, s)) != hipSuccess)

@@ -1,0 +1,115 @@
+"""Launches of few tiles (64 x 64 tiles whose waves divide the contraction), and the fp32 products
+on the bf16 matrix cores.
+
+Steps and reads on shapes at the edges of that form: fewer K steps than waves, K steps that four
+does not divide, contractions of two parts that end on different waves, one token, tokens just
+past a tile, one past the largest launch the form takes, against the CPU oracle at the parity
+suite's bars.  Then fp32 operands that three bf16 planes cannot hold (infinities, NaN, values that
+round to an infinity in bf16), against 64 bits."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from paper_2608_17616_amd import configs, mone
+from tests.gpu_helpers import DeviceProblem, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+C = configs.MoneConfig
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return torch
+
+
+# d_model, d_hidden, d_kv, seg_len, tokens per segment
+SHAPES = {
+    "one_step": (64, 64, 64, 64, [64, 1]),          # K = 64: one K step of bf16, two of fp32
+    "three_steps": (192, 320, 64, 65, [65, 64]),    # K = 192 + 320 in two parts
+    "five_steps": (320, 576, 128, 130, [130, 129, 7]),
+    "seven_nine": (448, 576, 192, 257, [257, 191]),
+    "last_row": (256, 1024, 64, 512, [449]),        # 8 x 16 tiles; the last row of one token
+}
+
+
+def tol(cfg):  # the parity suite's bars
+    return 1e-4 if cfg.act_dtype == "f32" else 2e-2
+
+
+@pytest.mark.parametrize("loss", ["mse_sum", "nip"])
+@pytest.mark.parametrize("act", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_small_steps(torch_cuda, shape, act, loss):
+    d, h, d_kv, T, ns = SHAPES[shape]
+    cfg = C(shape, n_layers=3, d_model=d, d_hidden=h, d_kv=d_kv, seg_len=T, n_context=sum(ns),
+            act_dtype=act, lr=2e-2 if loss == "mse_sum" else 5e-3, loss=loss)
+    print(shape, act, loss, flush=True)
+    prob = DeviceProblem(cfg, [0, 2])
+    sess = mone.TtlSession(cfg, prob.wkv, prob.w1, prob.w2)
+    for s, n in enumerate(ns):
+        sess.segment(prob.segment(s, n), n)
+    xq, hx = prob.query(70)
+    kv = torch_cuda.empty(3, 70, cfg.d_out, dtype=torch_cuda.float32, device="cuda")
+    sess.memory_kv(xq, kv)
+    torch_cuda.cuda.synchronize()
+    sess.close()
+    for l in (0, 2):
+        p = prob.host[l]
+        o1, o2, _ = orc.ttl_run(p["x"], p["w1"], p["w2"], p["wkv"], cfg.lr, cfg.loss)
+        assert rel_l2(prob.w1[l].cpu().numpy() - p["w1"], o1 - p["w1"]) < tol(cfg)
+        assert rel_l2(prob.w2[l].cpu().numpy() - p["w2"], o2 - p["w2"]) < tol(cfg)
+        assert rel_l2(kv[l].cpu().numpy(), orc.memory_kv(hx[l], o1, o2)) < tol(cfg)
+
+
+# q and the widths choose the tile: 64 x 64; 64 x 256 with the contraction split; 128 x 128
+@pytest.mark.parametrize("L,d,h,d_kv,q", [(2, 128, 192, 64, 40), (9, 512, 4096, 1024, 40),
+                                          (9, 128, 2048, 1024, 200)])
+def test_fp32_products_error(torch_cuda, L, d, h, d_kv, q):
+    """The read against 64 bits.  Splitting an fp32 value into three bf16 planes is exact and the
+    products left out are below 2^-26 of the sum of magnitudes, so what remains is the
+    accumulation in fp32 of at most d (or h) products: sqrt(K) roundings of 2^-24, taken of the
+    sum of magnitudes."""
+    torch = torch_cuda
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    w1, w2, xq = rnd(L, h, d) * d ** -0.5, rnd(L, 2 * d_kv, h) * h ** -0.5, rnd(L, q, d)
+    cfg = C("prod", L, d, h, d_kv, 256, 256, "f32", 1e-3)
+    sess = mone.TtlSession(cfg, rnd(L, 2 * d_kv, d), w1, w2)
+    kv = torch.empty(L, q, 2 * d_kv, device="cuda")
+    sess.memory_kv(xq, kv)
+    sess.close()
+    a = torch.nn.functional.silu(xq.double() @ w1.double().transpose(1, 2).contiguous())
+    ref = a @ w2.double().transpose(1, 2).contiguous()
+    assert float((kv.double() - ref).norm() / ref.norm()) < (d ** 0.5 + h ** 0.5) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("L,h,q", [(2, 192, 40), (9, 4096, 40), (9, 2048, 200)])
+def test_fp32_products_not_finite(torch_cuda, L, h, q):
+    """An infinite or NaN weight gives what fp32 arithmetic gives, in its layer only, and a finite
+    value that rounds to an infinity in bf16 is multiplied as it is."""
+    torch = torch_cuda
+    d, d_kv = 128, 1024 if h > 1000 else 64
+    g = torch.Generator(device="cuda").manual_seed(9)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")  # noqa: E731
+    w1, w2, xq = rnd(L, h, d) * d ** -0.5, rnd(L, 2 * d_kv, h) * h ** -0.5, rnd(L, q, d)
+    w2[0, 3, 11] = float("inf")     # column 3 of layer 0's output alone
+    w2[0, 7, 5] = float("nan")
+    w1[1, 17, 9] = 3.4e38           # finite; above the largest bf16 value
+    xq[1, :, 9] = 2e-38
+    cfg = C("special", L, d, h, d_kv, 256, 256, "f32", 1e-3)
+    sess = mone.TtlSession(cfg, rnd(L, 2 * d_kv, d), w1, w2)
+    kv = torch.empty(L, q, 2 * d_kv, device="cuda")
+    sess.memory_kv(xq, kv)
+    sess.close()
+    a = torch.nn.functional.silu(xq.double() @ w1.double().transpose(1, 2).contiguous())
+    a, wt = a.cpu(), w2.double().transpose(1, 2).contiguous().cpu()
+    ref, out = (a @ wt).numpy(), kv.double().cpu().numpy()
+    assert np.array_equal(np.isnan(out), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert inf[0, :, 3].all() and np.array_equal(out[inf], ref[inf])
+    ok = np.isfinite(ref)
+    assert np.isfinite(out[ok]).all() and rel_l2(out[ok], ref[ok]) < 1e-5
